@@ -220,8 +220,8 @@ int oc_suffix_prefill_layer_noalloc(const void *q, const void *k_new, const void
  *   h    = act . W_down             [T][H]
  *   qkv  = h . W_qkv                [T][(n_q + 2 n_kv) d]   the next layer's projection
  * Each stage is rounded to bf16 (nearest even).  Norms, residuals and biases
- * are left out.  The GEMMs run in rocBLAS, the gating in a kernel of this
- * library.  Weights are device bf16, [K][N] row-major (input features by
+ * are left out.  On few rows the GEMMs run in kernels of this library, else
+ * in rocBLAS.  Weights are device bf16, [K][N] row-major (input features by
  * output features), one matrix per layer back to back, 16-byte aligned;
  * caller-owned and only read. */
 typedef struct {
@@ -244,8 +244,9 @@ typedef struct {
 
 /* The chain above for one layer; attn_out is device bf16 [tokens][H] (the
  * attention output, as oc_suffix_prefill_layer writes it).  tokens == 0 is
- * not an error.  Asynchronous on `stream`; the first call on a stream
- * creates the GEMM library's handle for it (which may allocate). */
+ * not an error.  Asynchronous on `stream`; the library
+ * keeps a 32 MiB workspace and a GEMM library handle per stream, each made by
+ * the first call on that stream that needs it (which allocates). */
 int oc_rest_of_layer(const void *attn_out, int64_t tokens, const oc_layout *layout,
                      const oc_layer_weights *weights, int32_t layer, const oc_layer_buffers *buffers,
                      void *stream);

@@ -28,18 +28,10 @@
 #include <math.h>
 
 #include <algorithm>
-#include <mutex>
 
-#include "common.hpp"
+#include "mfma_tiles.hpp"
 
 namespace oc {
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-typedef float f32x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int PAGE = 16;          // tokens per pool page (attention requires page_size 16)
 constexpr int KB = 64;            // keys per block = 4 pages
@@ -49,7 +41,6 @@ constexpr int WAVE_ROWS = 32 * QB;
 constexpr int TILE_ROWS = WAVES * WAVE_ROWS;
 constexpr int THREADS = WAVES * 64;
 constexpr int TARGET_WGS = 256;   // one workgroup per CU
-constexpr int kMaxDevices = 64;   // devices a process may launch on
 #ifndef OC_BATCH_ROUNDS
 #define OC_BATCH_ROUNDS 2
 #endif
@@ -93,61 +84,8 @@ __device__ inline float half_swap_sum(float x) {
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-// Workgroup barrier that waits only for this wavefront's LDS operations.
-// (__syncthreads() would also wait for every outstanding global load, which
-// would stall the register prefetch of the block after next.)
-__device__ inline void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
 // tile row r of a 32-key MFMA tile reads physical key perm(r): bits 2 and 3 swapped
 __device__ inline int key_perm(int r) { return (r & ~12) | ((r & 4) << 1) | ((r & 8) >> 1); }
-
-// LDS element offset of 16-byte column c of K tile row r (D/8 columns per row)
-template <int D>
-__device__ inline int k_lds(int r, int c) {
-    constexpr int NS = D / 8;
-    return r * D + ((c ^ (r & (NS - 1))) << 3);
-}
-
-// XOR applied to the 16-byte column index of V tile row r.  The transposing
-// reads of the PV operand take 4 dims x 4 keys per 16-lane group, from rows
-// that differ in their low key bits; this spreads those rows over all banks.
-template <int D>
-__device__ inline int v_swz(int r) {
-    if constexpr (D == 128) return 4 * (r & 3);
-    else return 4 * ((r >> 1) & 1);
-}
-
-typedef __attribute__((address_space(3))) void *lds_ptr_t;
-typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
-
-// one 16-byte global -> LDS copy per lane from `base` (wave-uniform) plus the
-// lane's byte offset; the wavefront's 64 lanes fill 1 KiB of LDS starting at
-// `lds_chunk`, lane i at byte 16*i.  Issued as inline
-// assembly on purpose: the compiler treats every outstanding global->LDS copy
-// as a possible writer of any LDS address, and would make each operand read
-// of the current tile wait (vmcnt(0)) for the copies of the blocks still in
-// flight, which serialises the prefetch.  The kernel orders these copies
-// itself: wait_vmcnt before the per-block barrier, which is the only point
-// where a tile becomes readable, and a buffer is refilled only after every
-// wavefront has passed the barrier that follows its last read.
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Winline-asm"   // m0 is written here and read by nothing else in these kernels
-__device__ inline void dma16(const void *base, uint32_t lane_off, uint16_t *lds_chunk) {
-    const uint32_t m0 = (uint32_t)(uintptr_t)(lds_ptr_t)lds_chunk;   // LDS byte address, wave-uniform
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-                 :
-                 : "v"(lane_off), "s"(base), "s"(m0)
-                 : "memory", "m0");
-}
-#pragma clang diagnostic pop
-
-template <int N>
-__device__ inline void wait_vmcnt() {
-    static_assert(N == 0 || N == 2 || N == 4, "unexpected count");
-    if constexpr (N == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    else if constexpr (N == 2) asm volatile("s_waitcnt vmcnt(2)" ::: "memory");
-    else asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
-}
 
 // Per-wavefront running state of the online softmax for its 32 query rows.
 template <int D>
@@ -158,25 +96,6 @@ struct WaveState {
     float m, l;          // running maximum (log2 units) and sum of this lane's row
 };
 
-// Matrix phase of a wavefront: O^T += V^T P for the previous block (PV:
-// 16 MFMAs at d = 128, each V^T fragment from two transposing LDS reads),
-// then S^T = K Q^T for the current block (S: 16 MFMAs, K fragments from the
-// swizzled tile, the two 32-key halves alternating so that consecutive MFMAs
-// are independent).  Written as one flat sequence whose operand reads run
-// LOOKAHEAD MFMAs ahead (with PV, the first LOOKAHEAD come preloaded, see
-// prefetch_vt); a scheduling fence after every MFMA keeps that order (left
-// alone, the compiler hoists every read to the top and runs out of VGPRs).
-// V^T fragment n of a PV pass (n = 8-key group * D/32 + dim tile)
-template <int D>
-__device__ __forceinline__ bf16x8 load_vt(const uint16_t *V, const int (&voff)[D / 32], int n) {
-    constexpr int NET = D / 32;
-    const int et = n % NET, g4 = n / NET;     // g4 = 2*half + key group
-    const uint16_t *vp = V + voff[et] + ((g4 >> 1) * 32 + (g4 & 1) * 16) * D;
-    const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4 *)vp);
-    const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4 *)(vp + 4 * D));
-    return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-}
-
 // The first LOOKAHEAD V^T fragments of a PV pass, read ahead of the barrier
 // that opens the matrix phase (the V tile of the previous block is already
 // readable there), so the phase starts without waiting on LDS.
@@ -186,6 +105,14 @@ __device__ __forceinline__ void prefetch_vt(const uint16_t *V, const int (&voff)
     for (int n = 0; n < LOOKAHEAD; ++n) pre[n] = load_vt<D>(V, voff, n);
 }
 
+// Matrix phase of a wavefront: O^T += V^T P for the previous block (PV:
+// 16 MFMAs at d = 128, each V^T fragment from two transposing LDS reads),
+// then S^T = K Q^T for the current block (S: 16 MFMAs, K fragments from the
+// swizzled tile, the two 32-key halves alternating so that consecutive MFMAs
+// are independent).  Written as one flat sequence whose operand reads run
+// LOOKAHEAD MFMAs ahead (with PV, the first LOOKAHEAD come preloaded, see
+// prefetch_vt); a scheduling fence after every MFMA keeps that order (left
+// alone, the compiler hoists every read to the top and runs out of VGPRs).
 template <int D, bool PV, bool S>
 __device__ __forceinline__ void matrix_phase(WaveState<D> &w, const uint16_t *V, const int (&voff)[D / 32],
                                              const uint16_t *K, const bf16x8 (&qop)[D / 16], int krow, int half,
@@ -409,20 +336,9 @@ __global__ __launch_bounds__(THREADS) void attn_fwd_kernel(KBatch batch) {
     w.m = -__builtin_inff();
     w.l = 0.f;
     const int krow = key_perm(col);
-    // Transposing V reads: in each 16-lane group, source lane 4j+q names the
-    // four dims [4q, 4q+4) of key row j; output lane i then holds dim i of
-    // the four rows.  Group k covers dims 16*(k%2) + [0,16) and keys
-    // 8*(k/2) + [0,4) of the 16-key slice (the second read adds 4 rows).
     int voff[D / 32];
-    {
-        const int k16 = lane >> 4, j = (lane >> 2) & 3, q4 = lane & 3;
-        const int key = 8 * (k16 >> 1) + j;
 #pragma unroll
-        for (int et = 0; et < D / 32; ++et) {
-            const int dim = et * 32 + 16 * (k16 & 1) + 4 * q4;
-            voff[et] = key * D + (((dim >> 3) ^ v_swz<D>(key)) << 3) + (dim & 7);
-        }
-    }
+    for (int et = 0; et < D / 32; ++et) voff[et] = vt_offset<D>(lane, et);
 
     // Mask of one block: keys [0, pe) of the block are prefix keys, suffix
     // keys start at ps, and a row sees suffix key k (block position) when
@@ -802,19 +718,8 @@ static hipError_t launch_d(const AttnPlan *pl, const AttnArgs *a, int n, hipStre
         grid += 8 * ((batch.req[k].n_groups + 7) / 8) * (int64_t)pl[i].m_tiles;
     }
     if (grid > attention_max_grid()) return hipErrorInvalidConfiguration;
-    // the kernel's dynamic LDS above the default limit, set once per device
-    // (any thread may make the first launch on a device)
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
+    const hipError_t e = allow_dynamic_lds<&attn_fwd_kernel<D>>((int)attn_lds_bytes<D>());
     if (e != hipSuccess) return e;
-    if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
-    static std::once_flag lds_once[kMaxDevices];
-    static hipError_t lds_status[kMaxDevices];
-    std::call_once(lds_once[dev], [dev] {
-        lds_status[dev] = hipFuncSetAttribute(reinterpret_cast<const void *>(&attn_fwd_kernel<D>),
-                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)attn_lds_bytes<D>());
-    });
-    if (lds_status[dev] != hipSuccess) return lds_status[dev];
     if (grid > 0) hipLaunchKernelGGL(attn_fwd_kernel<D>, dim3((unsigned)grid), dim3(THREADS), attn_lds_bytes<D>(), s, batch);
     // the split merge of every request that has splits, in one launch
     constexpr int RPB = 256 / (D / 4);

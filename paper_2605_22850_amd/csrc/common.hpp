@@ -126,6 +126,16 @@ size_t layer_buffer_bytes(const oc_layout &l, int32_t ffn_dim, int64_t tokens, s
 // drop the GEMM library's state bound to a stream about to be destroyed
 void forget_blas_stream(hipStream_t s);
 
+// ---- GEMM for few rows -----------------------------------------------------------
+// y[M][N] = x[M][K] . w[K][N], bf16 row-major, 16-byte aligned; with `act`,
+// also act[M][N/2] = silu(y[:, :N/2]) * y[:, N/2:].  `ws` holds split
+// partials, GEMM_WORKSPACE_BYTES of device memory that nothing else uses
+// while the call runs.
+constexpr size_t GEMM_WORKSPACE_BYTES = (size_t)32 << 20;
+bool gemm_rows_applies(int64_t M, int64_t K, int64_t N);
+hipError_t launch_gemm_rows(const uint16_t *x, const uint16_t *w, uint16_t *y, uint16_t *act, void *ws, int64_t M,
+                            int64_t K, int64_t N, hipStream_t s);
+
 // ---- emulated compute window ---------------------------------------------------
 // holds stream `s` for `seconds` (at most OC_MAX_WINDOW_S, checked by callers)
 hipError_t launch_compute_window(double seconds, hipStream_t s);

@@ -1,8 +1,9 @@
 // Rest-of-layer compute window: what a transformer layer runs on the miss
 // tokens besides the attention (the C_l of eq. (3); every layer has the same
 // projections and feed-forward network, Section 3.6).  Four bf16 GEMMs with
-// fp32 accumulation (O, gate|up, down, next layer's QKV) go to rocBLAS; the
-// SiLU gating between them is a kernel of its own.
+// fp32 accumulation (O, gate|up, down, next layer's QKV): on few rows the
+// library's own kernels, which stream the weights, else rocBLAS, with the SiLU
+// gating as a kernel of its own.
 #include <rocblas/rocblas.h>
 
 #include <algorithm>
@@ -38,24 +39,30 @@ __global__ __launch_bounds__(256) void silu_mul_kernel(const uint16_t *gu, uint1
     *reinterpret_cast<u32x4 *>(act + t * 8 * F8 + c * 8) = __builtin_bit_cast(u32x4, __builtin_convertvector(r, bf16x8));
 }
 
-// One rocBLAS handle per (device, stream): a handle's workspace must not be
-// shared by GEMMs running on different streams.  Handles live until the
-// process ends, or until forget_blas_stream() for streams the library owns.
+// Per (device, stream): a rocBLAS handle and the few-row GEMM's workspace,
+// each made when first needed; neither may be shared by GEMMs running on
+// different streams.  They live until the process ends, or until
+// forget_blas_stream() for streams the library owns.
+struct StreamState {
+    rocblas_handle handle = nullptr;
+    void *ws = nullptr;
+};
 static std::mutex g_blas_mu;
-static std::map<std::pair<int, hipStream_t>, rocblas_handle> g_blas;
+static std::map<std::pair<int, hipStream_t>, StreamState> g_blas;
 
-static int blas_for(hipStream_t s, rocblas_handle *out) {
+static int stream_state(hipStream_t s, StreamState **out) {
     int dev = 0;
     OC_HIP(hipGetDevice(&dev));
-    auto key = std::make_pair(dev, s);
-    auto it = g_blas.find(key);
-    if (it == g_blas.end()) {
-        rocblas_handle h = nullptr;
-        if (rocblas_create_handle(&h) != rocblas_status_success) return fail(OC_EHIP, "rocblas_create_handle failed");
-        it = g_blas.emplace(key, h).first;
+    *out = &g_blas[std::make_pair(dev, s)];
+    return OC_OK;
+}
+
+static int blas_for(StreamState *st, hipStream_t s) {
+    if (!st->handle && rocblas_create_handle(&st->handle) != rocblas_status_success) {
+        st->handle = nullptr;
+        return fail(OC_EHIP, "rocblas_create_handle failed");
     }
-    if (rocblas_set_stream(it->second, s) != rocblas_status_success) return fail(OC_EHIP, "rocblas_set_stream failed");
-    *out = it->second;
+    if (rocblas_set_stream(st->handle, s) != rocblas_status_success) return fail(OC_EHIP, "rocblas_set_stream failed");
     return OC_OK;
 }
 
@@ -63,7 +70,8 @@ void forget_blas_stream(hipStream_t s) {
     std::lock_guard<std::mutex> g(g_blas_mu);
     for (auto it = g_blas.begin(); it != g_blas.end();) {
         if (it->first.second == s) {
-            rocblas_destroy_handle(it->second);
+            if (it->second.handle) rocblas_destroy_handle(it->second.handle);
+            if (it->second.ws) (void)hipFree(it->second.ws);
             it = g_blas.erase(it);
         } else {
             ++it;
@@ -90,24 +98,44 @@ static int gemm(rocblas_handle h, const uint16_t *X, const uint16_t *W, uint16_t
 int launch_rest_of_layer(const LayerArgs &a, hipStream_t s) {
     if (a.T == 0) return OC_OK;
     std::lock_guard<std::mutex> g(g_blas_mu);
-    rocblas_handle h = nullptr;
-    int rc = blas_for(s, &h);
+    StreamState *st = nullptr;
+    int rc = stream_state(s, &st);
     if (rc) return rc;
     const int64_t widest = std::max(std::max(2 * a.F, a.H), a.NQKV);
     const int64_t rb = std::max<int64_t>(1, (INT64_C(1) << 29) / widest);
+    // one product of the chain on m rows; with `act`, the gating as well
+    auto product = [&](const uint16_t *x, const uint16_t *w, uint16_t *y, uint16_t *act, int64_t m, int64_t K,
+                       int64_t N) -> int {
+        if (gemm_rows_applies(m, K, N)) {
+            // without memory for its workspace the product goes to the library
+            if (!st->ws && hipMalloc(&st->ws, GEMM_WORKSPACE_BYTES) != hipSuccess) {
+                (void)hipGetLastError();
+                st->ws = nullptr;
+            }
+            if (st->ws) {
+                OC_HIP(launch_gemm_rows(x, w, y, act, st->ws, m, K, N, s));
+                return OC_OK;
+            }
+        }
+        int r = blas_for(st, s);
+        if (r || (r = gemm(st->handle, x, w, y, m, K, N))) return r;
+        if (act) {
+            const int64_t n = m * (N / 16);
+            hipLaunchKernelGGL(silu_mul_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, y, act,
+                               (int64_t)(N / 16), n);
+            OC_HIP(hipGetLastError());
+        }
+        return OC_OK;
+    };
     for (int64_t r0 = 0; r0 < a.T; r0 += rb) {
         const int64_t m = std::min(rb, a.T - r0);
         const uint16_t *x = a.attn_out + r0 * a.H;
         uint16_t *o = a.o + r0 * a.H, *gu = a.gu + r0 * 2 * a.F, *act = a.act + r0 * a.F;
         uint16_t *hh = a.h + r0 * a.H, *qkv = a.qkv + r0 * a.NQKV;
-        if ((rc = gemm(h, x, a.w_o, o, m, a.H, a.H))) return rc;
-        if ((rc = gemm(h, o, a.w_gu, gu, m, a.H, 2 * a.F))) return rc;
-        const int64_t n = m * (a.F / 8);
-        hipLaunchKernelGGL(silu_mul_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, gu, act,
-                           (int64_t)(a.F / 8), n);
-        OC_HIP(hipGetLastError());
-        if ((rc = gemm(h, act, a.w_down, hh, m, a.F, a.H))) return rc;
-        if ((rc = gemm(h, hh, a.w_qkv, qkv, m, a.H, a.NQKV))) return rc;
+        if ((rc = product(x, a.w_o, o, nullptr, m, a.H, a.H))) return rc;
+        if ((rc = product(o, a.w_gu, gu, act, m, a.H, 2 * a.F))) return rc;
+        if ((rc = product(act, a.w_down, hh, nullptr, m, a.F, a.H))) return rc;
+        if ((rc = product(hh, a.w_qkv, qkv, nullptr, m, a.H, a.NQKV))) return rc;
     }
     return OC_OK;
 }
