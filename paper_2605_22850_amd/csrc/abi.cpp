@@ -131,9 +131,9 @@ static int check_attention_layout(const oc_layout &l) {
     return OC_OK;
 }
 
-int check_attention_args(const oc_layout &l, int64_t Tp, int64_t Ts) {
+int check_attention_args(const oc_layout &l, int64_t Tp, int64_t Ts, AttnPlan *plan) {
     int rc = check_attention_layout(l);
-    return rc ? rc : check_attention_shape(l, Tp, Ts);
+    return rc ? rc : check_attention_shape(l, Tp, Ts, plan);
 }
 
 // ---- workspace of the allocation-free attention entry point ----------------
@@ -376,10 +376,8 @@ size_t oc_attention_workspace_bytes(const oc_layout *layout, int64_t prefix_toke
         fail(OC_EINVAL, "layout is NULL");
         return 0;
     }
-    if (check_attention_args(*layout, prefix_tokens, suffix_tokens)) return 0;
     AttnPlan p;
-    plan_attention(*layout, prefix_tokens, suffix_tokens, &p);
-    return p.total;
+    return check_attention_args(*layout, prefix_tokens, suffix_tokens, &p) ? 0 : p.total;
 }
 
 }  // extern "C"
@@ -398,13 +396,12 @@ static int check_attention_call(const void *q, const void *k_new, const void *v_
     if ((rc = check_table(block_table, l))) return rc;
     if (layer < 0 || layer >= l.num_layers) return fail(OC_ERANGE, "layer out of range");
     if (suffix_tokens < 1) return fail(OC_EINVAL, "suffix_tokens must be >= 1");
-    if ((rc = check_attention_shape(l, block_table->num_tokens, suffix_tokens))) return rc;
+    if ((rc = check_attention_shape(l, block_table->num_tokens, suffix_tokens, plan))) return rc;
     if (!q || !k_new || !v_new || !out) return fail(OC_EINVAL, "NULL tensor");
     if (block_table->num_tokens > 0 && !kv_pool->base) return fail(OC_EINVAL, "NULL pool base");
     if (!aligned(q, 16) || !aligned(k_new, 16) || !aligned(v_new, 16) || !aligned(out, 16) ||
         !aligned(kv_pool->base, 16))
         return fail(OC_EALIGN, "q, k_new, v_new, out and pool base must be 16-byte aligned");
-    plan_attention(l, block_table->num_tokens, suffix_tokens, plan);
     return OC_OK;
 }
 

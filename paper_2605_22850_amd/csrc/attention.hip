@@ -28,6 +28,7 @@
 #include <math.h>
 
 #include <algorithm>
+#include <cmath>
 
 #include "mfma_tiles.hpp"
 
@@ -82,6 +83,26 @@ __device__ inline float half_swap_max(float x) {
 __device__ inline float half_swap_sum(float x) {
     auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// Workgroup wg of a launch -> its (KV head, split) group and row tile; false
+// past the last.  Workgroup w runs on XCD w % 8.  With a multiple of 8 groups
+// all row tiles of a group get consecutive slots on one XCD, so their K/V
+// re-reads hit that XCD's L2.  With other counts that would leave XCDs idle
+// (4 groups: half of them), so the tiles are dealt out one by one.  Either
+// way the last row tile comes first: under the causal mask later rows see
+// more suffix keys, and dispatching the longest tiles first keeps them out of
+// the tail.
+__device__ inline bool tile_of(int wg, int m_tiles, int n_groups, int &gamma, int &mt) {
+    if (n_groups & 7) {
+        gamma = wg % n_groups;
+        mt = m_tiles - 1 - wg / n_groups;
+        return mt >= 0;
+    }
+    const int xcd = wg & 7, local = wg >> 3;
+    gamma = (local / m_tiles) * 8 + xcd;
+    mt = m_tiles - 1 - local % m_tiles;
+    return gamma < n_groups;
 }
 
 // tile row r of a 32-key MFMA tile reads physical key perm(r): bits 2 and 3 swapped
@@ -242,14 +263,8 @@ __global__ __launch_bounds__(THREADS) void attn_fwd_kernel(KBatch batch) {
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = lane & 31, half = lane >> 5;
 
-    // XCD-aware decode: workgroup w runs on XCD w % 8; all row tiles of one
-    // (KV head, split) group get consecutive slots on the same XCD, the last
-    // row tile first: under the causal mask later rows see more suffix keys,
-    // and dispatching the longest tiles first keeps them out of the tail
-    const int xcd = wg & 7, local = wg >> 3;
-    const int gamma = (local / m_tiles) * 8 + xcd;
-    if (gamma >= n_groups) return;
-    const int mt = m_tiles - 1 - local % m_tiles;
+    int gamma, mt;
+    if (!tile_of(wg, m_tiles, n_groups, gamma, mt)) return;
     const int g = gamma / n_split, split = gamma - g * n_split;
 
     const int row = mt * TILE_ROWS + wave * WAVE_ROWS + col;
@@ -487,6 +502,347 @@ __global__ __launch_bounds__(THREADS) void attn_fwd_kernel(KBatch batch) {
     }
 }
 
+// ---------------------------------------------------------------------------
+// Few query rows: the wavefronts of a workgroup share one row tile and split
+// the keys among themselves.
+//
+// With few rows per KV head the kernel above pads its 256-row tile, and to
+// fill the CUs it splits the keys over so many workgroups that writing and
+// merging the fp32 partials costs more than the attention.  Here a workgroup
+// owns 32*QB rows and each of its NW wavefronts takes every NW-th unit of 32
+// keys, with a private ring of NB units in LDS: no barrier until the end, the
+// copies of a unit wait only for that wavefront's own reads.  A wavefront
+// refills its K buffer once S is computed and its V buffer after the PV
+// product.  The wavefronts' (m, l, O) are merged through LDS, so only NW times
+// fewer key ranges, if any, go through global partials.
+//
+// Two tiles: 32 rows (Q in registers), and 64 rows, where each copied unit
+// feeds twice the MFMAs (at d = 128 Q is then read from LDS: in registers it
+// would spill beside O).  One query row streams a 32K prefix at 4.4 TB/s; with
+// more rows the copies bound the 32-row tile (0.19 us per unit and CU at
+// d = 128, from L2) and the copies and MFMAs together the 64-row tile (0.27).
+// One layer on its own, us, 256-row tiles -> these (32 query / 8 KV heads, d
+// 128): 250 + 128 tokens 20.6 -> 8.4, 1024 + 128 24.8 -> 11.3, 4096 + 128
+// 28.1 -> 22.5, 32763 + 1 41.6 -> 30.4, 1024 + 512 33.4 -> 21.9.  Past some
+// 500 rows over 8K keys the 256-row tiles are the faster ones (65536 + 512:
+// 502 against 599).
+// ---------------------------------------------------------------------------
+constexpr int UNIT = 32;          // keys per unit: two pages
+constexpr int NW = 8;             // wavefronts of a workgroup
+
+template <int D, int QB>
+struct WaysShape {
+    static constexpr int ROWS = 32 * QB;
+    static constexpr int TILE = UNIT * D;                       // elements of one K (or V) unit
+    static constexpr int ND = TILE * 2 / 1024;                  // 1 KiB copies per K (or V) unit
+    static constexpr int CPP = ND / 2;                          // copies per page
+    static constexpr int KROWS = 512 / D;                       // key rows per copy
+    static constexpr int RING = 2 * TILE * 2;                   // bytes per wavefront: a K and a V unit, ...
+    static_assert(RING == 32 * D * 4, "... later the wavefront's O of 32 rows");
+    static constexpr bool QLDS = QB * D > 128;                  // Q stays in LDS where it would spill
+    static constexpr int Q_BYTES = QLDS ? ROWS * D * 2 : 0;
+    static constexpr int LDS = NW * RING + Q_BYTES + NW * ROWS * 8;   // rings, Q, (m, l) per wavefront and row
+};
+
+template <int D, int QB>
+__global__ __launch_bounds__(NW * 64) void attn_ways_kernel(KParams p) {
+    using Sh = WaysShape<D, QB>;
+    constexpr int ND = Sh::ND, CPP = Sh::CPP, TILE = Sh::TILE, NET = D / 32, NDS = D / 16;
+    extern __shared__ __align__(1024) uint16_t lds[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int col = lane & 31, half = lane >> 5;
+
+    int gamma, mt;
+    if (!tile_of((int)blockIdx.x, p.m_tiles, p.n_groups, gamma, mt)) return;
+    const int g = gamma / p.n_split, split = gamma - g * p.n_split;
+    const int rows = (int)p.rows, Tp = (int)p.Tp, Ts = (int)p.Ts, n_pre_pages = (int)p.n_pre_pages;
+    const int grp = p.grp, nq = p.nq, nkv = p.nkv;
+    const float scale_log2 = p.scale_log2;
+    const __attribute__((address_space(4))) int32_t *pages_c =
+        (const __attribute__((address_space(4))) int32_t *)p.pages;
+
+    // this split's units, clipped to what the tile's last row sees
+    int u0 = split * (int)p.blocks_per_split, u1 = u0 + (int)p.blocks_per_split;
+    {
+        int row_hi = (mt + 1) * Sh::ROWS - 1;
+        if (row_hi > rows - 1) row_hi = rows - 1;
+        const int last_page = n_pre_pages + row_hi / grp / PAGE;
+        const int n_units = last_page / 2 + 1;
+        if (u1 > n_units) u1 = n_units;
+    }
+    const int n = u1 > u0 + wave ? (u1 - u0 - wave + NW - 1) / NW : 0;     // units of this wavefront
+    auto unit = [&](int j) { return u0 + wave + j * NW; };
+
+    uint16_t *const ring = lds + wave * (Sh::RING / 2);
+    // Per-lane parts of the copy addresses (bytes): copy c of a page covers its
+    // key rows c * KROWS + rr0.  V's swizzle is the same in each (one offset,
+    // the rest in the scalar base); K's is not at d = 128.
+    const int rr0 = lane / (D / 8);
+    uint32_t klane[CPP];
+#pragma unroll
+    for (int c = 0; c < CPP; ++c)
+        klane[c] = (uint32_t)(rr0 * D + ((lane % (D / 8)) ^ ((c * Sh::KROWS + rr0) & (D / 8 - 1))) * 8) * 2;
+    const uint32_t vlane = (uint32_t)(rr0 * D + ((lane % (D / 8)) ^ v_swz<D>(rr0)) * 8) * 2;
+    auto load_pids = [&](int j, int32_t (&pid)[2]) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int v = unit(j) * 2 + h;
+            pid[h] = v < n_pre_pages ? pages_c[v] : 0;
+        }
+    };
+    // copy one unit's K (or V) rows: two pages of the pool, or suffix rows
+    auto issue = [&](int j, const int32_t (&pid)[2], bool is_k, uint16_t *dst) {
+        const uint16_t *const pool = is_k ? p.pool_k : p.pool_v, *const dense = is_k ? p.k_new : p.v_new;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int v = unit(j) * 2 + h;
+            if (v < n_pre_pages) {
+                const uint16_t *base = pool + ((int64_t)pid[h] * nkv + g) * (PAGE * D);
+#pragma unroll
+                for (int c = 0; c < CPP; ++c)
+                    dma16(base + c * Sh::KROWS * D, is_k ? klane[c] : vlane, dst + (h * CPP + c) * 512);
+            } else {
+#pragma unroll
+                for (int c = 0; c < CPP; ++c) {
+                    // suffix token; rows past the last one repeat it (masked)
+                    int T = (v - n_pre_pages) * PAGE + c * Sh::KROWS + rr0;
+                    if (T > Ts - 1) T = Ts - 1;
+                    const uint32_t rw = ((uint32_t)(T * nkv + g) * D - (uint32_t)rr0 * D) * 2;
+                    dma16(dense, rw + (is_k ? klane[c] : vlane), dst + (h * CPP + c) * 512);
+                }
+            }
+        }
+    };
+    uint16_t *const K = ring, *const V = ring + TILE;
+    uint16_t *const q_lds = lds + NW * Sh::RING / 2;
+    float2 *const ml = reinterpret_cast<float2 *>(reinterpret_cast<unsigned char *>(lds) + NW * Sh::RING + Sh::Q_BYTES);
+
+    // Q: to LDS (swizzled as K), or each lane's row to registers
+    bf16x8 qop[Sh::QLDS ? 1 : QB][NDS];
+    int tok[QB];
+    const int tok0 = mt * Sh::ROWS / grp;
+    if constexpr (Sh::QLDS) {
+        const uint16_t *qbase = p.q + ((int64_t)tok0 * nq + g * grp) * D;
+#pragma unroll
+        for (int u = 0; u < Sh::Q_BYTES / 1024 / NW; ++u) {
+            const int c = u * NW + wave;
+            const int r = c * Sh::KROWS + lane / (D / 8);
+            int row = mt * Sh::ROWS + r;
+            if (row > rows - 1) row = rows - 1;                  // rows past the last repeat it (not stored)
+            const uint32_t e = (uint32_t)((row / grp - tok0) * nq + row % grp) * D +
+                               ((lane % (D / 8)) ^ (r & (D / 8 - 1))) * 8;
+            dma16(qbase, e * 2, q_lds + c * 512);
+        }
+    }
+    int32_t pid[2];
+    if (n > 0) {
+        load_pids(0, pid);
+        issue(0, pid, true, K);
+        issue(0, pid, false, V);
+    }
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+        const int row = mt * Sh::ROWS + qb * 32 + col;
+        const bool ok = row < rows;
+        tok[qb] = ok ? row / grp : 0;
+        if constexpr (!Sh::QLDS) {
+            const uint16_t *qr = p.q + ((int64_t)tok[qb] * nq + g * grp + (ok ? row % grp : 0)) * D + half * 8;
+#pragma unroll
+            for (int ds = 0; ds < NDS; ++ds)
+                qop[qb][ds] = ok ? *reinterpret_cast<const bf16x8 *>(qr + ds * 16) : bf16x8{};
+        }
+    }
+    int voff[NET];
+#pragma unroll
+    for (int et = 0; et < NET; ++et) voff[et] = vt_offset<D>(lane, et);
+    const int krow = key_perm(col);
+
+    f32x16 o[QB][NET];
+    float m[QB], l[QB];
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+        m[qb] = -__builtin_inff();
+        l[qb] = 0.f;
+#pragma unroll
+        for (int et = 0; et < NET; ++et) o[qb][et] = f32x16{};
+    }
+    const int full_pre_pages = Tp / PAGE;
+    // Q has arrived: a wait the compiler sees, so that it places none of its
+    // own (for every copy in flight) inside the loop.  It waits for the first
+    // unit too, which the loop needs next.
+    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
+    if constexpr (Sh::QLDS) lds_barrier();
+
+    for (int j = 0; j < n; ++j) {
+        const int u = unit(j);
+        const bool refill = j + 1 < n;
+        if (refill) load_pids(j + 1, pid);
+        wait_vmcnt<ND>();                 // K of this unit has landed: at most its V is in flight
+        f32x16 s[QB];
+        {
+            bf16x8 kf[NDS], qf[QB][NDS];
+            auto load = [&](int ds) {
+                kf[ds] = *reinterpret_cast<const bf16x8 *>(&K[k_lds<D>(krow, ds * 2 + half)]);
+#pragma unroll
+                for (int qb = 0; qb < QB; ++qb)
+                    if constexpr (Sh::QLDS)
+                        qf[qb][ds] = *reinterpret_cast<const bf16x8 *>(&q_lds[k_lds<D>(qb * 32 + col, ds * 2 + half)]);
+                    else
+                        qf[qb][ds] = qop[qb][ds];
+            };
+            constexpr int AHEAD = Sh::QLDS ? 2 : NDS;      // operands read ahead of their use
+#pragma unroll
+            for (int ds = 0; ds < AHEAD; ++ds) load(ds);
+#pragma unroll
+            for (int ds = 0; ds < NDS; ++ds) {
+                if (ds + AHEAD < NDS) load(ds + AHEAD);
+#pragma unroll
+                for (int qb = 0; qb < QB; ++qb)
+                    s[qb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ds], qf[qb][ds], ds == 0 ? f32x16{} : s[qb], 0, 0, 0);
+                if constexpr (Sh::QLDS) __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");      // K is read: its buffer may be refilled
+        if (refill) issue(j + 1, pid, true, K);
+
+        if ((u + 1) * 2 > full_pre_pages) {     // the prefix's partial last page, or suffix keys
+            const int ps = n_pre_pages * PAGE - u * UNIT, pe = Tp - u * UNIT;
+            const bool partial_prefix = ps > 0 && pe < (ps < UNIT ? ps : UNIT);
+            const bool unseen_suffix = ps < UNIT && UNIT - 1 - ps > tok0;
+            if (partial_prefix || unseen_suffix) {
+                const int sh = 8 * half;
+#pragma unroll
+                for (int qb = 0; qb < QB; ++qb)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) {
+                        const int kin = i < 8 ? i : 8 + i;                    // key in the unit, less 8*half
+                        const uint32_t keep =
+                            0u - (uint32_t)((kin < pe - sh) | ((kin >= ps - sh) & (kin <= tok[qb] + ps - sh)));
+                        s[qb][i] = __uint_as_float((__float_as_uint(s[qb][i]) & keep) | (0xff800000u & ~keep));
+                    }
+            }
+        }
+        // online softmax, as softmax_phase: the running maximum is raised, and
+        // O rescaled, only when a unit's maximum exceeds it by 2^RESCALE_SLACK
+        bf16x8 pp[QB][2];
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) {
+            float mx[2] = {-__builtin_inff(), -__builtin_inff()};
+#pragma unroll
+            for (int i = 0; i < 16; ++i) mx[i & 1] = fmaxf(mx[i & 1], s[qb][i]);
+            const float mu = half_swap_max(fmaxf(mx[0], mx[1])) * scale_log2;
+            if (__any(mu > m[qb] + RESCALE_SLACK)) {
+                const float mn = fmaxf(m[qb], mu);
+                const float alpha = __builtin_amdgcn_exp2f(m[qb] - (mn == -__builtin_inff() ? 0.f : mn));
+                m[qb] = mn;
+                l[qb] *= alpha;
+#pragma unroll
+                for (int et = 0; et < NET; ++et) o[qb][et] *= alpha;
+            }
+            const float m_use = m[qb] == -__builtin_inff() ? 0.f : m[qb];
+            typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+            const bf16x2 ones = {(__bf16)1.f, (__bf16)1.f};
+            float ls[2] = {0.f, 0.f};
+#pragma unroll
+            for (int hf = 0; hf < 2; ++hf) {
+                f32x8 e;
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+                    e[i] = __builtin_amdgcn_exp2f(fmaf(s[qb][hf * 8 + i], scale_log2, -m_use));
+                const bf16x8 b = __builtin_convertvector(e, bf16x8);
+                pp[qb][hf] = b;
+                ls[0] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(b, b, 0, 1), ones, ls[0], false);
+                ls[1] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(b, b, 2, 3), ones, ls[1], false);
+                ls[0] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(b, b, 4, 5), ones, ls[0], false);
+                ls[1] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(b, b, 6, 7), ones, ls[1], false);
+            }
+            l[qb] += ls[0] + ls[1];
+        }
+        if (refill) wait_vmcnt<ND>();     // V has landed
+        else wait_vmcnt<0>();
+        if ((u + 1) * 2 > full_pre_pages && u * 2 <= full_pre_pages && full_pre_pages < n_pre_pages) {
+            // zero the partial prefix page's slots past Tp, which may hold
+            // anything: masked keys then contribute exactly nothing
+            const int pg = full_pre_pages - u * 2, k0 = Tp % PAGE;
+            for (int i = lane; i < D * (PAGE - k0); i += 64) V[(pg * PAGE + k0) * D + i] = 0;
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        }
+        {
+            bf16x8 vf[2 * NET];
+            constexpr int AHEAD = Sh::QLDS ? 3 : 2 * NET;
+#pragma unroll
+            for (int i = 0; i < AHEAD; ++i) vf[i] = load_vt<D>(V, voff, i);
+#pragma unroll
+            for (int i = 0; i < 2 * NET; ++i) {
+                if (i + AHEAD < 2 * NET) vf[i + AHEAD] = load_vt<D>(V, voff, i + AHEAD);
+#pragma unroll
+                for (int qb = 0; qb < QB; ++qb)
+                    o[qb][i % NET] =
+                        __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[i], pp[qb][i / NET], o[qb][i % NET], 0, 0, 0);
+                if constexpr (Sh::QLDS) __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");      // V is read
+        if (refill) issue(j + 1, pid, false, V);
+    }
+
+    // ---- merge the wavefronts, 32 rows at a time ----
+    // Row r's 16-byte chunks are stored XOR r, so that neither the writes (one
+    // row per lane) nor the reads (one chunk per lane) meet on a bank.
+    constexpr int CH = D / 4;                                   // chunks of four floats per row
+    float *const mine = reinterpret_cast<float *>(ring);
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+        const float lt = half_swap_sum(l[qb]);
+        if (half == 0) ml[wave * Sh::ROWS + qb * 32 + col] = float2{m[qb], lt};
+    }
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+        if (qb > 0) __syncthreads();                            // the last rows have been read
+#pragma unroll
+        for (int et = 0; et < NET; ++et)
+#pragma unroll
+            for (int vq = 0; vq < 4; ++vq) {
+                const f32x4 a = {o[qb][et][vq * 4], o[qb][et][vq * 4 + 1], o[qb][et][vq * 4 + 2], o[qb][et][vq * 4 + 3]};
+                const int ch = et * 8 + vq * 2 + half;
+                *reinterpret_cast<f32x4 *>(mine + col * D + ((ch ^ col) & (CH - 1)) * 4) = a;
+            }
+        __syncthreads();
+        for (int i = tid; i < 32 * CH; i += NW * 64) {
+            const int r = i / CH, ch = i % CH;
+            const int row = mt * Sh::ROWS + qb * 32 + r;
+            if (row >= rows) break;
+            float2 w[NW];
+            float M = -__builtin_inff();
+#pragma unroll
+            for (int k = 0; k < NW; ++k) {
+                w[k] = ml[k * Sh::ROWS + qb * 32 + r];
+                M = fmaxf(M, w[k].x);
+            }
+            const float Mu = M == -__builtin_inff() ? 0.f : M;
+            float L = 0.f;
+            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int k = 0; k < NW; ++k) {
+                const float e = __builtin_amdgcn_exp2f(w[k].x - Mu);
+                L += e * w[k].y;
+                acc += e * *reinterpret_cast<const f32x4 *>(reinterpret_cast<const float *>(lds) + k * (Sh::RING / 4) +
+                                                           r * D + ((ch ^ r) & (CH - 1)) * 4);
+            }
+            if (p.n_split == 1) {
+                const float inv = L > 0.f ? 1.f / L : 0.f;
+                uint16_t *orow = p.out + ((int64_t)(row / grp) * nq + g * grp + row % grp) * D;
+                *reinterpret_cast<bf16x4 *>(orow + ch * 4) = __builtin_convertvector(acc * inv, bf16x4);
+            } else {
+                const int64_t prow = ((int64_t)split * nkv + g) * p.rows_pad + row;
+                *reinterpret_cast<f32x4 *>(p.o_part + prow * D + ch * 4) = acc;
+                if (ch == 0) *reinterpret_cast<float2 *>(p.ml_part + prow * 2) = float2{M, L};
+            }
+        }
+    }
+}
+
 template <int D>
 constexpr size_t attn_lds_bytes() { return (size_t)4 * 2 * KB * D * 2; }
 
@@ -575,7 +931,7 @@ __global__ __launch_bounds__(256) void attn_combine_batch_kernel(KBatch batch) {
 static size_t round_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 // Tiles and key blocks of one request; the split count is set apart.
-static AttnPlan plan_shape(const oc_layout &lay, int64_t Tp, int64_t Ts) {
+static AttnPlan plan_shape(const oc_layout &lay, int64_t Tp, int64_t Ts, int tile_rows) {
     AttnPlan p{};
     p.Tp = Tp;
     p.Ts = Ts;
@@ -584,10 +940,12 @@ static AttnPlan plan_shape(const oc_layout &lay, int64_t Tp, int64_t Ts) {
     p.grp = p.nq / p.nkv;
     p.d = lay.head_dim;
     p.rows = Ts * p.grp;
-    p.m_tiles = (int)((p.rows + TILE_ROWS - 1) / TILE_ROWS);
+    p.tile_rows = tile_rows;
+    p.m_tiles = (int)((p.rows + p.tile_rows - 1) / p.tile_rows);
     p.n_pre_pages = (Tp + PAGE - 1) / PAGE;
     p.n_suf_pages = (Ts + PAGE - 1) / PAGE;
-    p.n_blocks = (p.n_pre_pages + p.n_suf_pages + 3) / 4;
+    const int pages_per_block = (tile_rows == TILE_ROWS ? KB : UNIT) / PAGE;
+    p.n_blocks = (p.n_pre_pages + p.n_suf_pages + pages_per_block - 1) / pages_per_block;
     return p;
 }
 
@@ -597,7 +955,7 @@ static void plan_splits(AttnPlan &p, int64_t ns) {
     if (ns < 1) ns = 1;
     p.blocks_per_split = (p.n_blocks + ns - 1) / ns;
     p.n_split = (int)((p.n_blocks + p.blocks_per_split - 1) / p.blocks_per_split);
-    const int64_t rows_pad = (int64_t)p.m_tiles * TILE_ROWS;
+    const int64_t rows_pad = (int64_t)p.m_tiles * p.tile_rows;
     size_t off = 0;
     p.off_o = off;
     if (p.n_split > 1) off = round_up(off + (size_t)p.n_split * p.nkv * rows_pad * p.d * 4, 256);
@@ -606,12 +964,71 @@ static void plan_splits(AttnPlan &p, int64_t ns) {
     p.total = off > 256 ? off : 256;   // never 0: a size of 0 reports an unsupported shape
 }
 
-// One request alone: split the keys so that its row tiles fill the CUs.
+// Estimated time (us) of one request's attention under a plan: the rule that
+// picks the row tile and the split count.  Fitted to 192 shapes (n_q/n_kv/d of
+// 32/8/128, 64/8/128, 4/1/128, 32/4/64, 8/8/64, 4/2/64; prefixes of 100 to
+// 50000 tokens, suffixes of 1 to 1600) with up to 40 plans each: over them the
+// plan it picks is 1 % slower than the best one measured, on average.
+struct PlanCost {
+    double block128, block64;   // one key block of one workgroup, at d = 128 and 64
+    double round;               // the least time of one block per wavefront
+    double start, spread;       // launch, first copies, epilogue; extra when every CU holds a workgroup
+    double wave;                // each further workgroup per CU
+};
+static const PlanCost COST_32 = {0.182, 0.112, 0.63, 4.2, 3.2, 1.4}, COST_64 = {0.259, 0.167, 1.38, 5.6, 3.5, 3.8},
+                      COST_256 = {1.49, 1.17, 0.88, 6.2, 1.6, 1.0};
+
+static double plan_cost(const AttnPlan &p) {
+    const PlanCost &k = p.tile_rows == 32 ? COST_32 : p.tile_rows == 64 ? COST_64 : COST_256;
+    const double tiles = (double)p.nkv * p.m_tiles, wgs = tiles * p.n_split, bps = (double)p.blocks_per_split;
+    // average share of the key blocks a row tile sees under the causal mask
+    const double pages = (double)(p.n_pre_pages + p.n_suf_pages);
+    const double seen = p.m_tiles > 1 ? (p.n_pre_pages + 0.5 * (p.n_suf_pages + 1)) / pages : 1.0;
+    const double per_cu = wgs / TARGET_WGS;
+    const double block = p.d == 128 ? k.block128 : k.block64;
+    double body = block * bps;
+    if (per_cu > 1) body *= seen * std::max(1.0, std::min(std::ceil(per_cu), per_cu + 0.55));
+    body = std::max(body, k.round * (p.tile_rows == TILE_ROWS ? 1.0 : std::ceil(bps / NW)));
+    // all inputs and the output once at 5 TB/s
+    const double hbm = 4.0 * p.d * ((double)p.nq * p.Ts + (double)p.nkv * (p.Tp + p.Ts)) / 5e6;
+    body = std::sqrt(body * body + hbm * hbm);
+    double t = k.start + k.spread * std::min(per_cu, 1.0) + body;
+    if (per_cu > 1) t += k.wave * (std::ceil(per_cu) - 1);
+    // the merge's launch, and its partials written and read
+    if (p.n_split > 1) t += 2.4 + 0.556e-6 * p.n_split * p.nkv * p.rows * p.d * 4;
+    return t;
+}
+
+// One request alone.  256-row tiles with the keys split so that they fill the
+// CUs; or another tile or split count where the estimate says that it is at
+// least 4 % faster.  The workspace asked for is always that of the first plan
+// (a caller may hold one of that size), so a plan that needs more is left.
 int plan_attention(const oc_layout &lay, int64_t Tp, int64_t Ts, AttnPlan *pl) {
-    AttnPlan p = plan_shape(lay, Tp, Ts);
-    const int64_t tiles = (int64_t)p.nkv * p.m_tiles;
-    plan_splits(p, (TARGET_WGS + tiles - 1) / tiles);
-    *pl = p;
+    AttnPlan best = plan_shape(lay, Tp, Ts, TILE_ROWS);
+    const int64_t fill = (TARGET_WGS + (int64_t)best.nkv * best.m_tiles - 1) / ((int64_t)best.nkv * best.m_tiles);
+    plan_splits(best, fill);
+    const size_t ws_bytes = best.total;
+    double least = 0.96 * plan_cost(best);
+    for (const int tile : {32, 64, TILE_ROWS}) {
+        // the 64-row tile copies its Q rows with 32-bit offsets from its first token's
+        if (tile == 64 && (int64_t)65 * lay.num_q_heads * lay.head_dim * 2 > INT32_MAX) continue;
+        AttnPlan p = plan_shape(lay, Tp, Ts, tile);
+        const int64_t tiles = (int64_t)p.nkv * p.m_tiles;
+        if (tiles > 4 * TARGET_WGS && tile != TILE_ROWS) continue;     // long suffixes: whole 256-row tiles
+        for (const int ns : {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 24, 32, 48, 64, 96, 128}) {
+            if (ns > 1 && (ns > p.n_blocks || ns * tiles > 2 * TARGET_WGS)) break;
+            if (tile == TILE_ROWS && ns > fill) break;
+            plan_splits(p, ns);
+            if (p.total > ws_bytes) continue;
+            const double t = plan_cost(p);
+            if (t < least) {
+                least = t;
+                best = p;
+            }
+        }
+    }
+    best.total = ws_bytes;
+    *pl = best;
     return OC_OK;
 }
 
@@ -622,7 +1039,7 @@ int plan_attention(const oc_layout &lay, int64_t Tp, int64_t Ts, AttnPlan *pl) {
 int plan_attention_batch(const oc_layout &lay, const int64_t *Tp, const int64_t *Ts, int n, AttnPlan *plans) {
     int64_t tiles = 0, work = 0, longest = 1;
     for (int i = 0; i < n; ++i) {
-        plans[i] = plan_shape(lay, Tp[i], Ts[i]);
+        plans[i] = plan_shape(lay, Tp[i], Ts[i], TILE_ROWS);
         const int64_t t = (int64_t)plans[i].nkv * plans[i].m_tiles;
         tiles += t;
         work += t * plans[i].n_blocks;
@@ -641,7 +1058,7 @@ int plan_attention_batch(const oc_layout &lay, const int64_t *Tp, const int64_t 
     return OC_OK;
 }
 
-int64_t attention_grid(const AttnPlan &p) { return 8 * (((int64_t)p.nkv * p.n_split + 7) / 8) * p.m_tiles; }
+int64_t attention_grid(const AttnPlan &p) { return ((int64_t)p.nkv * p.n_split * p.m_tiles + 7) / 8 * 8; }
 
 // a dispatch holds at most 2^32 - 1 work-items along x
 int64_t attention_max_grid() { return OC_MAX_GRID_ITEMS / THREADS; }
@@ -650,7 +1067,7 @@ size_t attention_lds_bytes(int head_dim) {
     return head_dim == 64 ? attn_lds_bytes<64>() : head_dim == 128 ? attn_lds_bytes<128>() : 0;
 }
 
-int check_attention_shape(const oc_layout &l, int64_t Tp, int64_t Ts) {
+int check_attention_shape(const oc_layout &l, int64_t Tp, int64_t Ts, AttnPlan *plan) {
     if (l.head_dim != 64 && l.head_dim != 128) return fail(OC_ESHAPE, "attention supports head_dim 64 or 128");
     if (l.page_size != PAGE) return fail(OC_ESHAPE, "attention supports page_size 16");
     if (Tp < 0 || Ts < 1) return fail(OC_EINVAL, "attention needs prefix_tokens >= 0 and suffix_tokens >= 1");
@@ -662,11 +1079,12 @@ int check_attention_shape(const oc_layout &l, int64_t Tp, int64_t Ts) {
     const int64_t grp = l.num_q_heads / l.num_kv_heads;
     if (Ts * grp > (int64_t)1 << 30) return fail(OC_ERANGE, "suffix_tokens * (n_q / n_kv) exceeds 2^30");
     AttnPlan p;
-    plan_attention(l, Tp, Ts, &p);
-    if (attention_grid(p) > attention_max_grid())
+    if (!plan) plan = &p;
+    plan_attention(l, Tp, Ts, plan);
+    if (attention_grid(*plan) > attention_max_grid())
         return fail(OC_ERANGE, "attention grid of more than " + std::to_string(attention_max_grid()) + " workgroups");
     // the split merge runs d/4 work-items per (KV head, row)
-    if ((int64_t)p.nkv * p.rows * (p.d / 4) > OC_MAX_GRID_ITEMS)
+    if ((int64_t)plan->nkv * plan->rows * (plan->d / 4) > OC_MAX_GRID_ITEMS)
         return fail(OC_ERANGE, "split merge grid exceeds 2^32 work-items");
     return OC_OK;
 }
@@ -686,7 +1104,7 @@ static KParams make_params(const AttnPlan &pl, const AttnArgs &a) {
     p.Tp = pl.Tp;
     p.Ts = pl.Ts;
     p.rows = pl.rows;
-    p.rows_pad = (int64_t)pl.m_tiles * TILE_ROWS;
+    p.rows_pad = (int64_t)pl.m_tiles * pl.tile_rows;
     p.n_pre_pages = pl.n_pre_pages;
     p.n_suf_pages = pl.n_suf_pages;
     p.n_blocks = pl.n_blocks;
@@ -715,7 +1133,7 @@ static hipError_t launch_d(const AttnPlan *pl, const AttnArgs *a, int n, hipStre
         const int i = order[k];
         batch.req[k] = make_params<D>(pl[i], a[i]);
         batch.first_wg[k] = (int32_t)grid;
-        grid += 8 * ((batch.req[k].n_groups + 7) / 8) * (int64_t)pl[i].m_tiles;
+        grid += attention_grid(pl[i]);
     }
     if (grid > attention_max_grid()) return hipErrorInvalidConfiguration;
     const hipError_t e = allow_dynamic_lds<&attn_fwd_kernel<D>>((int)attn_lds_bytes<D>());
@@ -743,7 +1161,28 @@ static hipError_t launch_d(const AttnPlan *pl, const AttnArgs *a, int n, hipStre
     return hipGetLastError();
 }
 
+template <int D, int QB>
+static hipError_t launch_ways(const AttnPlan &pl, const AttnArgs &a, hipStream_t s) {
+    using Sh = WaysShape<D, QB>;
+    static_assert(Sh::LDS <= (int)CU_LDS_BYTES, "rings larger than the LDS");
+    const KParams p = make_params<D>(pl, a);
+    const hipError_t e = allow_dynamic_lds<&attn_ways_kernel<D, QB>>(Sh::LDS);
+    if (e != hipSuccess) return e;
+    const int64_t grid = attention_grid(pl);
+    static_assert(NW * 64 == THREADS, "the grid's limit is shared");
+    if (grid > attention_max_grid()) return hipErrorInvalidConfiguration;
+    hipLaunchKernelGGL((attn_ways_kernel<D, QB>), dim3((unsigned)grid), dim3(NW * 64), Sh::LDS, s, p);
+    if (p.n_split > 1) {
+        constexpr int RPB = 256 / (D / 4);
+        const int64_t blocks = ((int64_t)p.nkv * p.rows + RPB - 1) / RPB;
+        hipLaunchKernelGGL(attn_combine_kernel<D>, dim3((unsigned)blocks), dim3(256), 0, s, p);
+    }
+    return hipGetLastError();
+}
+
 hipError_t launch_attention(const AttnPlan &pl, const AttnArgs &a, hipStream_t s) {
+    if (pl.tile_rows == 32) return pl.d == 128 ? launch_ways<128, 1>(pl, a, s) : launch_ways<64, 1>(pl, a, s);
+    if (pl.tile_rows == 64) return pl.d == 128 ? launch_ways<128, 2>(pl, a, s) : launch_ways<64, 2>(pl, a, s);
     if (pl.d == 128) return launch_d<128>(&pl, &a, 1, s);
     return launch_d<64>(&pl, &a, 1, s);
 }

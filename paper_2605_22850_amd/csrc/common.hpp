@@ -150,7 +150,8 @@ struct AttnPlan {
     int32_t n_split;           // key-range splits
     int64_t n_pre_pages;       // ceil(Tp / 16)
     int64_t n_suf_pages;       // ceil(Ts / 16)
-    int64_t n_blocks;          // key blocks of 64 keys over prefix then suffix pages
+    int32_t tile_rows;         // rows of one row tile: 256, or 32 or 64 where its wavefronts split the keys
+    int64_t n_blocks;          // key blocks (64 keys; 32 for the smaller tiles) over prefix then suffix pages
     int64_t blocks_per_split;
     // workspace carve-up (byte offsets): split partials
     size_t off_o, off_ml, total;
@@ -159,11 +160,11 @@ int plan_attention(const oc_layout &lay, int64_t Tp, int64_t Ts, AttnPlan *plan)
 // Shapes the attention kernels can index: the layout (head_dim 64 or 128,
 // page_size 16; OC_ESHAPE otherwise) and the 32-bit limits of their
 // arithmetic (OC_ERANGE): suffix K/V byte offsets, key positions, rows and
-// the grids of both kernels.
-int check_attention_shape(const oc_layout &lay, int64_t Tp, int64_t Ts);
+// the grids of both kernels.  On OC_OK `plan`, if given, is the request's plan.
+int check_attention_shape(const oc_layout &lay, int64_t Tp, int64_t Ts, AttnPlan *plan = nullptr);
 // check_attention_shape after the layout's own checks (positive fields, GQA
 // head ratio, alignment multiples)
-int check_attention_args(const oc_layout &lay, int64_t Tp, int64_t Ts);
+int check_attention_args(const oc_layout &lay, int64_t Tp, int64_t Ts, AttnPlan *plan = nullptr);
 // workgroups of the attention launch of one plan
 int64_t attention_grid(const AttnPlan &p);
 // at most this many workgroups in one attention launch (all its requests)
