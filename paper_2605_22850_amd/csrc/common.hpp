@@ -99,9 +99,12 @@ struct AppendArgs {
     int32_t n_kv, d, Ps;
     // filled by the launcher
     int64_t region;
-    int32_t d8;
+    int32_t d8, lg_d8, lg_nkv, lg_ps;
 };
 hipError_t launch_append(AppendArgs a, hipStream_t s);
+// the appends of up to MAX_APPEND_BATCH requests of one pool, in one launch
+constexpr int MAX_APPEND_BATCH = 16;
+hipError_t launch_append_batch(const AppendArgs *a, int n, hipStream_t s);
 // OC_OK when bt also holds pages for suffix_tokens tokens behind its prefix
 int check_append_table(const oc_block_table *bt, const oc_layout &l, int64_t suffix_tokens);
 // arguments for appending `suffix_tokens` tokens of `layer` behind bt->num_tokens

@@ -836,8 +836,6 @@ static int run_pipeline(Context *c, const oc_request *reqs, int32_t n_reqs, oc_r
     std::vector<hipEvent_t> done(c->events.begin() + 1 + 2 * n_items, c->events.begin() + 1 + 2 * n_items + n_done);
     std::vector<double> produced(n_items, -1.0);
 
-    // one layer's compute for request `ri` on `st`: attention, then the suffix
-    // append and the rest of the layer when asked for
     std::string layer_msg;       // why the rest of the layer failed to enqueue
     auto attn_args = [&](int32_t ri, int32_t layer, unsigned char *ws) {
         const oc_request &r = reqs[ri];
@@ -857,20 +855,19 @@ static int run_pipeline(Context *c, const oc_request *reqs, int32_t n_reqs, oc_r
         return a;
     };
     // after a request's attention: the suffix append and the rest of the layer
-    auto after_attention = [&](int32_t ri, int32_t layer, const AttnArgs &a, hipStream_t st) -> hipError_t {
+    auto layer_append = [&](int32_t ri, int32_t layer, const AttnArgs &a) {
         const oc_request &r = reqs[ri];
-        hipError_t e = hipSuccess;
-        if (c->opts.append_suffix)
-            e = launch_append(append_args(&c->pool, r.block_table, layer, a.k_new, a.v_new, r.suffix_tokens), st);
-        if (e == hipSuccess && c->has_layer) {
-            unsigned char *lb = static_cast<unsigned char *>(c->lbuf) + (emu ? ri : 0) * lb_stride;
-            const oc_layer_buffers bufs{lb + loff[0], lb + loff[1], lb + loff[2], lb + loff[3], lb + loff[4]};
-            if (launch_rest_of_layer(layer_args(l, c->lw, layer, a.out, r.suffix_tokens, bufs), st) != OC_OK) {
-                layer_msg = oc_last_error();
-                return hipErrorLaunchFailure;
-            }
+        return append_args(&c->pool, r.block_table, layer, a.k_new, a.v_new, r.suffix_tokens);
+    };
+    auto rest_of_layer = [&](int32_t ri, int32_t layer, const AttnArgs &a, hipStream_t st) -> hipError_t {
+        if (!c->has_layer) return hipSuccess;
+        unsigned char *lb = static_cast<unsigned char *>(c->lbuf) + (emu ? ri : 0) * lb_stride;
+        const oc_layer_buffers bufs{lb + loff[0], lb + loff[1], lb + loff[2], lb + loff[3], lb + loff[4]};
+        if (launch_rest_of_layer(layer_args(l, c->lw, layer, a.out, reqs[ri].suffix_tokens, bufs), st) != OC_OK) {
+            layer_msg = oc_last_error();
+            return hipErrorLaunchFailure;
         }
-        return e;
+        return hipSuccess;
     };
     // one layer's compute for request `ri` on `st`
     auto enqueue_attention = [&](int32_t ri, int32_t layer, hipStream_t st) -> hipError_t {
@@ -879,15 +876,24 @@ static int run_pipeline(Context *c, const oc_request *reqs, int32_t n_reqs, oc_r
         plan_attention(l, r.prefix_tokens, r.suffix_tokens, &p);
         const AttnArgs a = attn_args(ri, layer, static_cast<unsigned char *>(c->ws) + (emu ? ri : 0) * ws_stride);
         hipError_t e = launch_attention(p, a, st);
-        return e == hipSuccess ? after_attention(ri, layer, a, st) : e;
+        if (e == hipSuccess && c->opts.append_suffix) e = launch_append(layer_append(ri, layer, a), st);
+        return e == hipSuccess ? rest_of_layer(ri, layer, a, st) : e;
     };
-    // one layer's compute for every request: one attention launch over all
+    // one layer's compute for every request: one attention launch over all,
+    // and one append (eight launches of 256 tokens each took 42 us per layer
+    // behind a 470 us attention)
     auto enqueue_layer_batch = [&](int32_t layer, hipStream_t st) -> hipError_t {
         std::vector<AttnArgs> args(n_reqs);
         for (int32_t ri = 0; ri < n_reqs; ++ri)
             args[ri] = attn_args(ri, layer, static_cast<unsigned char *>(c->ws) + bws_off[ri]);
         hipError_t e = launch_attention_batch(bplan.data(), args.data(), n_reqs, st);
-        for (int32_t ri = 0; ri < n_reqs && e == hipSuccess; ++ri) e = after_attention(ri, layer, args[ri], st);
+        if (e == hipSuccess && c->opts.append_suffix) {
+            static_assert(MAX_APPEND_BATCH >= MAX_ATTN_BATCH, "one append launch per batched layer");
+            std::vector<AppendArgs> app(n_reqs);
+            for (int32_t ri = 0; ri < n_reqs; ++ri) app[ri] = layer_append(ri, layer, args[ri]);
+            e = launch_append_batch(app.data(), n_reqs, st);
+        }
+        for (int32_t ri = 0; ri < n_reqs && e == hipSuccess; ++ri) e = rest_of_layer(ri, layer, args[ri], st);
         return e;
     };
 
@@ -1198,7 +1204,10 @@ static int run_pipeline(Context *c, const oc_request *reqs, int32_t n_reqs, oc_r
                 a.n_kv = l.num_kv_heads;
                 a.d = l.head_dim;
                 a.Ps = l.page_size;
-                e = launch_ingest(a, (bt.num_tokens + l.page_size - 1) / l.page_size, c->copy, step > 0);
+                // beside an attention: past the first item; batched, past the
+                // first layer, whose attention waits for all its ingests
+                e = launch_ingest(a, (bt.num_tokens + l.page_size - 1) / l.page_size, c->copy,
+                                  batched ? it.layer > 0 : step > 0);
             }
             if (e == hipSuccess) e = hipEventRecord(ingested[k], c->copy);
             // batched: the copy stream runs in order, so the layer's last

@@ -129,6 +129,31 @@ def test_pipeline_appends_every_layer_and_keeps_outputs():
         assert_attention_close(base[r][rs.L - 1], rs.expected_out(r, rs.L - 1), f"request {r}")
 
 
+# (nq, nkv, d, prefixes, suffixes): shift and division decodes, an empty
+# prefix, suffixes of one token and of several workgroups, the most requests
+# one launch takes and one more
+BATCH_APPEND_CASES = {
+    "pow2": (8, 2, 128, [256, 0, 64, 512], [40, 1, 300, 17]),
+    "three-kv-heads": (6, 3, 64, [128, 48], [33, 130]),
+    "sixteen": (4, 2, 64, [16 * i for i in range(16)], [1 + 3 * i for i in range(16)]),
+    "seventeen": (4, 2, 64, [16 * i for i in range(17)], [1 + 3 * i for i in range(17)]),
+}
+
+
+@pytest.mark.parametrize("name", list(BATCH_APPEND_CASES))
+def test_batched_pipeline_appends_every_request(name):
+    import paper_2605_22850_amd as oc
+    nq, nkv, d, pre, suf = BATCH_APPEND_CASES[name]
+    print(f"[writeback] batched append, {name}", flush=True)
+    need = sum(-(-(p + s) // 16) for p, s in zip(pre, suf))
+    rs = RequestSet(2, nq, nkv, d, pre, suf, need + 9, seed=23, suffix_room=True).upload(with_payload=True)
+    _run(rs, oc.OC_MODE_DEVICE_STAGED, append_suffix=True)
+    got = from_dev(rs.d_pool).reshape(rs.pool_shape())
+    assert np.array_equal(got, rs.expected_pool(appended=True)), "pool differs from the oracle's scatter + append"
+    for r in range(len(pre)):
+        assert_attention_close(from_dev(rs.reqs[r].out)[1], rs.expected_out(r, 1), f"{name} request {r}")
+
+
 def test_pipeline_append_needs_room_in_the_table():
     import paper_2605_22850_amd as oc
     print("[writeback] pipeline append validation", flush=True)
