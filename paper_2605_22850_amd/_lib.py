@@ -1,4 +1,5 @@
-"""ctypes binding of ``libobjectcache.so`` -- argument marshalling only.
+"""Binding of ``libobjectcache.so`` -- argument marshalling only, in ctypes and,
+for the single-layer calls, in the CPython module ``_marshal``.
 
 Every function here has the name of the C entry point it calls and does no
 arithmetic of the method: it turns torch tensors (device memory owned by the
@@ -92,6 +93,37 @@ class c_request_stats(ctypes.Structure):
 
 
 _lib = None
+_fast = None
+
+# the library's functions behind _marshal's, in the order its bind() takes them
+_FAST = ["oc_kv_layer_ingest", "oc_kv_chunks_ingest", "oc_kv_layer_gather", "oc_kv_chunks_gather",
+         "oc_kv_suffix_append", "oc_suffix_prefill_layer", "oc_suffix_prefill_layer_noalloc", "oc_rest_of_layer"]
+
+
+def _native():
+    """The marshalling module, bound to the loaded library."""
+    global _fast
+    if _fast is None:
+        L = lib()
+        path = os.path.join(_HERE, "_marshal.so")
+        if not os.path.exists(path):
+            raise ImportError(f"{path} is missing: build it with `python -m paper_2605_22850_amd.build`")
+        from importlib.machinery import ExtensionFileLoader
+        from importlib.util import module_from_spec, spec_from_file_location
+        spec = spec_from_file_location("_marshal", path, loader=ExtensionFileLoader("_marshal", path))
+        m = module_from_spec(spec)
+        spec.loader.exec_module(m)
+        m.bind(_current_stream, *(ctypes.cast(getattr(L, f), c_void_p).value for f in _FAST))
+        _fast = m
+    return _fast
+
+
+def _current_stream() -> int:
+    """Handle of torch's current stream on the current device."""
+    import torch
+    if torch.cuda.is_initialized():
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return torch.cuda.current_stream().cuda_stream
 
 
 def lib():
@@ -180,15 +212,6 @@ def _ptr(t) -> Optional[int]:
     return t.data_ptr()
 
 
-def _stream(stream) -> Optional[int]:
-    if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
-    if isinstance(stream, int):
-        return stream
-    return stream.cuda_stream
-
-
 def make_pool(pool, layout: Layout) -> c_kv_pool:
     return c_kv_pool(_ptr(pool), layout.c())
 
@@ -210,46 +233,30 @@ def oc_block_table_check(host_pages, num_tokens: int, num_pages: int, page_size:
 
 def oc_kv_layer_ingest(staging, num_chunks: int, pages, num_tokens: int, pool, layout: Layout, layer: int,
                        stream=None) -> None:
-    st = c_staging(_ptr(staging), num_chunks, layout.slice_bytes)
-    bt = make_table(pages, num_tokens)
-    kp = make_pool(pool, layout)
-    _check(lib().oc_kv_layer_ingest(ctypes.byref(st), ctypes.byref(bt), ctypes.byref(kp), layer, _stream(stream)))
+    _check(_native().kv_layer_ingest(staging, num_chunks, pages, num_tokens, pool, layout, layer, stream))
 
 
 def oc_kv_chunks_ingest(objects, num_chunks: int, first_chunk: int, pages, num_tokens: int, pool, layout: Layout,
                         stream=None) -> None:
     """Whole chunk objects (device, num_chunks * L * S bytes back to back) -> every layer of the pool."""
-    st = c_staging(_ptr(objects), num_chunks, layout.slice_bytes)
-    bt = make_table(pages, num_tokens)
-    kp = make_pool(pool, layout)
-    _check(lib().oc_kv_chunks_ingest(ctypes.byref(st), first_chunk, ctypes.byref(bt), ctypes.byref(kp),
-                                     _stream(stream)))
+    _check(_native().kv_chunks_ingest(objects, num_chunks, first_chunk, pages, num_tokens, pool, layout, stream))
 
 
 def oc_kv_layer_gather(pages, num_tokens: int, pool, layout: Layout, layer: int, staging_out, num_chunks: int,
                        stream=None) -> None:
-    bt = make_table(pages, num_tokens)
-    kp = make_pool(pool, layout)
-    _check(lib().oc_kv_layer_gather(ctypes.byref(bt), ctypes.byref(kp), layer, _ptr(staging_out), num_chunks,
-                                    layout.slice_bytes, _stream(stream)))
+    _check(_native().kv_layer_gather(pages, num_tokens, pool, layout, layer, staging_out, num_chunks, stream))
 
 
 def oc_kv_chunks_gather(pages, num_tokens: int, pool, layout: Layout, first_chunk: int, num_chunks: int,
                         objects_out, stream=None) -> None:
     """Pool -> chunk objects first_chunk .. first_chunk+num_chunks-1 (all layers) into device objects_out."""
-    bt = make_table(pages, num_tokens)
-    kp = make_pool(pool, layout)
-    _check(lib().oc_kv_chunks_gather(ctypes.byref(bt), ctypes.byref(kp), first_chunk, num_chunks,
-                                     _ptr(objects_out), _stream(stream)))
+    _check(_native().kv_chunks_gather(pages, num_tokens, pool, layout, first_chunk, num_chunks, objects_out, stream))
 
 
 def oc_kv_suffix_append(k_new, v_new, suffix_tokens: int, pages, num_tokens: int, pool, layout: Layout,
                         layer: int, stream=None) -> None:
     """One layer's suffix K/V (device [Ts][nkv][d]) -> pool positions num_tokens .. num_tokens+Ts-1."""
-    bt = make_table(pages, num_tokens)
-    kp = make_pool(pool, layout)
-    _check(lib().oc_kv_suffix_append(_ptr(k_new), _ptr(v_new), suffix_tokens, ctypes.byref(bt), ctypes.byref(kp),
-                                     layer, _stream(stream)))
+    _check(_native().kv_suffix_append(k_new, v_new, suffix_tokens, pages, num_tokens, pool, layout, layer, stream))
 
 
 @dataclass
@@ -270,11 +277,7 @@ class LayerWeights:
 def oc_rest_of_layer(attn_out, tokens: int, layout: Layout, weights: LayerWeights, layer: int, o, gate_up, act, h,
                      qkv, stream=None) -> None:
     """The rest of one layer on `tokens` rows of attn_out; stage outputs into o, gate_up, act, h, qkv."""
-    lay = layout.c()
-    w = weights.c()
-    b = c_layer_buffers(_ptr(o), _ptr(gate_up), _ptr(act), _ptr(h), _ptr(qkv))
-    _check(lib().oc_rest_of_layer(_ptr(attn_out), tokens, ctypes.byref(lay), ctypes.byref(w), layer,
-                                  ctypes.byref(b), _stream(stream)))
+    _check(_native().rest_of_layer(attn_out, tokens, layout, weights, layer, o, gate_up, act, h, qkv, stream))
 
 
 def oc_attention_workspace_bytes(layout: Layout, prefix_tokens: int, suffix_tokens: int) -> int:
@@ -287,21 +290,16 @@ def oc_attention_workspace_bytes(layout: Layout, prefix_tokens: int, suffix_toke
 
 def oc_suffix_prefill_layer(q, k_new, v_new, suffix_tokens: int, pool, layout: Layout, pages, num_tokens: int,
                             layer: int, out, workspace, stream=None) -> None:
-    bt = make_table(pages, num_tokens)
-    kp = make_pool(pool, layout)
-    _check(lib().oc_suffix_prefill_layer(_ptr(q), _ptr(k_new), _ptr(v_new), suffix_tokens, ctypes.byref(kp),
-                                         ctypes.byref(bt), layer, _ptr(out), _ptr(workspace), workspace.numel() *
-                                         workspace.element_size(), _stream(stream)))
+    _check(_native().suffix_prefill_layer(q, k_new, v_new, suffix_tokens, pool, layout, pages, num_tokens, layer, out,
+                                          workspace, stream))
 
 
 def oc_suffix_prefill_layer_noalloc(q, k_new, v_new, suffix_tokens: int, pool, layout: Layout, pages,
                                     num_tokens: int, layer: int, out, stream=None) -> None:
     """oc_suffix_prefill_layer without a workspace argument: the library's
     static per-device workspace holds the split partials."""
-    bt = make_table(pages, num_tokens)
-    kp = make_pool(pool, layout)
-    _check(lib().oc_suffix_prefill_layer_noalloc(_ptr(q), _ptr(k_new), _ptr(v_new), suffix_tokens, ctypes.byref(kp),
-                                                 ctypes.byref(bt), layer, _ptr(out), _stream(stream)))
+    _check(_native().suffix_prefill_layer_noalloc(q, k_new, v_new, suffix_tokens, pool, layout, pages, num_tokens,
+                                                  layer, out, stream))
 
 
 # ---------------------------------------------------------------------------
@@ -369,9 +367,11 @@ def oc_pipeline_run(ctx, requests: Sequence[Request], num_layers: int):
             co = r.chunk_objects
             if not co.flags["C_CONTIGUOUS"]:
                 raise ValueError("chunk_objects must be C-contiguous")
+            import numpy as np
             row = co.strides[0]
-            objs = (c_void_p * co.shape[0])(*[co.ctypes.data + j * row for j in range(co.shape[0])])
-            keep.append(objs)
+            ptrs = co.ctypes.data + row * np.arange(co.shape[0], dtype=np.uint64)
+            objs = ctypes.cast(ptrs.ctypes.data, POINTER(c_void_p))
+            keep.append(ptrs)
         creqs[i] = c_request(r.prefix_tokens, r.suffix_tokens, ctypes.pointer(bt), objs,
                              _ptr(r.device_payload), _ptr(r.q), _ptr(r.k_new), _ptr(r.v_new), _ptr(r.out),
                              r.layer_compute_s, r.arrival_s)

@@ -5,6 +5,7 @@ import glob
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
@@ -12,6 +13,9 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libobjectcache.so")
+# the Python binding's argument marshalling (a CPython module, host code only)
+MARSHAL_SRC = os.path.join(PKG, "native", "marshal.cpp")
+MARSHAL = os.path.join(PKG, "_marshal.so")
 BUILD_DIR = os.path.join(ROOT, "_build")
 ARCH = "gfx950"
 
@@ -43,6 +47,15 @@ def _compile(src: str, asan: bool = False) -> str:
     return obj
 
 
+def _build_marshal() -> None:
+    tmp = MARSHAL + ".tmp"
+    r = subprocess.run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-Wall", "-shared", "-fPIC", "-I", INCLUDE,
+                        "-I", sysconfig.get_paths()["include"], MARSHAL_SRC, "-o", tmp], capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"compiling {MARSHAL_SRC} failed:\n{r.stdout}\n{r.stderr}")
+    os.replace(tmp, MARSHAL)
+
+
 def build(verbose: bool = False, asan: bool = False) -> str:
     """Compile every source for gfx950 and link the library in-tree (with
     asan, the sanitizer build of the host code at ASAN_LIB instead)."""
@@ -60,6 +73,7 @@ def build(verbose: bool = False, asan: bool = False) -> str:
     if r.returncode != 0:
         raise RuntimeError(f"link failed:\n{r.stdout}\n{r.stderr}")
     os.replace(tmp, out)
+    _build_marshal()
     if verbose:
         print(f"built {out}")
     return out
