@@ -104,9 +104,9 @@ __global__ __launch_bounds__(kThreads, 8) void kv_ingest_rows_kernel(IngestArgs 
 }
 
 // Piece e of a payload numbered in payload order ([chunk][K|V][token][head]
-// [16-byte column]) -> its element offsets in the staging (from `staging`)
-// and in the pool (from `pool_k`), both including the layer step of
-// blockIdx.y.  With POW2 every divisor (d/8, KV heads, chunk size, page size)
+// [16-byte column]; from chunk blockIdx.z on) -> its element offsets in the
+// staging (from `staging`) and in the pool (from `pool_k`), both including the
+// layer step of blockIdx.y.  With POW2 every divisor (d/8, KV heads, chunk size, page size)
 // is a power of two and the decode is shifts and masks.
 template <bool POW2>
 __device__ inline void src_order_piece(const IngestArgs &a, int64_t e, int64_t &stage, int64_t &pool) {
@@ -129,7 +129,8 @@ __device__ inline void src_order_piece(const IngestArgs &a, int64_t e, int64_t &
         j = r3 >> 1;
         kv = (int)(r3 & 1);
     }
-    const int64_t T = a.token0 + j * a.G + t;
+    const int64_t jz = j + blockIdx.z;
+    const int64_t T = a.token0 + jz * a.G + t;
     int64_t q, slot;
     if (POW2) {
         q = T >> a.lg_ps;
@@ -139,7 +140,7 @@ __device__ inline void src_order_piece(const IngestArgs &a, int64_t e, int64_t &
         slot = T - q * a.Ps;
     }
     const int64_t page = a.pages[q];
-    stage = blockIdx.y * a.layer_step_staging + j * a.chunk_stride + (e - j * slice_pieces) * 8;
+    stage = blockIdx.y * a.layer_step_staging + jz * a.chunk_stride + (e - j * slice_pieces) * 8;
     pool = blockIdx.y * a.layer_step_pool + kv * a.region + ((page * a.n_kv + h) * a.Ps + slot) * (int64_t)a.d +
            c * 8;
 }
@@ -284,11 +285,27 @@ hipError_t launch_ingest(IngestArgs a, int64_t n_pages_used, hipStream_t s, bool
     return hipGetLastError();
 }
 
+// Grid over `pieces` 16-byte pieces of one layer.  Whole chunk objects go
+// object by object, so that the workgroups running at a time read (or write)
+// one stretch of memory instead of one layer's slice of many objects (64
+// objects of 64 tokens, 32 layers: ingest 5.25 -> 5.64 TB/s, a 64 MiB gather
+// 24.4 -> 22.4 us); `n` is then the pieces of one slice.  Short slices that
+// are no whole number of workgroups keep one run of pieces per layer.
+static dim3 payload_grid(const IngestArgs &a, int64_t &n) {
+    const int64_t chunks = a.num_tokens / a.G, slice = 2LL * a.G * a.n_kv * a.d8;
+    if (a.n_layers > 1 && chunks <= 65535 && (slice % kThreads == 0 || slice >= 16 * kThreads)) {
+        n = slice;
+        return dim3((unsigned)((n + kThreads - 1) / kThreads), (unsigned)a.n_layers, (unsigned)chunks);
+    }
+    n = a.num_tokens * 2 * a.n_kv * a.d8;
+    return dim3((unsigned)((n + kThreads - 1) / kThreads), (unsigned)a.n_layers);
+}
+
 hipError_t launch_chunks_ingest(IngestArgs a, hipStream_t s) {
     if (a.num_tokens == 0) return hipSuccess;
     const bool p2 = prepare(a);
-    const int64_t n = a.num_tokens * 2 * a.n_kv * a.d8;   // 16-byte pieces of one layer
-    const dim3 grid((unsigned)((n + kThreads - 1) / kThreads), (unsigned)a.n_layers);
+    int64_t n;
+    const dim3 grid = payload_grid(a, n);
     if (p2) hipLaunchKernelGGL(kv_ingest_src_kernel<true>, grid, dim3(kThreads), 0, s, a, n);
     else hipLaunchKernelGGL(kv_ingest_src_kernel<false>, grid, dim3(kThreads), 0, s, a, n);
     return hipGetLastError();
@@ -297,8 +314,8 @@ hipError_t launch_chunks_ingest(IngestArgs a, hipStream_t s) {
 hipError_t launch_gather(IngestArgs a, uint16_t *out, hipStream_t s) {
     if (a.num_tokens == 0) return hipSuccess;
     const bool p2 = prepare(a);
-    const int64_t n = a.num_tokens * 2 * a.n_kv * a.d8;   // 16-byte pieces of one layer
-    const dim3 grid((unsigned)((n + kThreads - 1) / kThreads), (unsigned)a.n_layers);
+    int64_t n;
+    const dim3 grid = payload_grid(a, n);
     if (p2) hipLaunchKernelGGL(kv_gather_src_kernel<true>, grid, dim3(kThreads), 0, s, a, out, n);
     else hipLaunchKernelGGL(kv_gather_src_kernel<false>, grid, dim3(kThreads), 0, s, a, out, n);
     return hipGetLastError();

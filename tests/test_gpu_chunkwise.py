@@ -157,7 +157,9 @@ def test_chunkwise_delivery_validation():
 
 # (G, Ps, n_chunks, nkv, d, L): whole chunk objects into pools whose pages are
 # not 16 slots, or whose head rows the attention does not take
-OBJECT_SHAPE_CASES = [(8, 24, 17, 2, 64, 3), (40, 8, 5, 3, 96, 2), (16, 32, 9, 8, 128, 4), (24, 48, 6, 1, 256, 2)]
+OBJECT_SHAPE_CASES = [(8, 24, 17, 2, 64, 3), (40, 8, 5, 3, 96, 2), (16, 32, 9, 8, 128, 4), (24, 48, 6, 1, 256, 2),
+                      # object by object: slices that end inside a workgroup, single layers
+                      (40, 16, 7, 5, 104, 3), (40, 16, 4, 5, 104, 1), (16, 16, 3, 16, 64, 2)]
 
 
 @pytest.mark.parametrize("G,Ps,n,nkv,d,L", OBJECT_SHAPE_CASES)
