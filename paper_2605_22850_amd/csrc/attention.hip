@@ -12,8 +12,8 @@
 //
 // Per 64-key block: the K and V rows of four pages ([slot][dim] pool blocks,
 // or for the suffix the k_new / v_new rows themselves) are copied straight
-// into token-major LDS tiles by the global->LDS load path, three blocks in
-// flight, one barrier per block.  The tiles' 16-byte columns are XOR-swizzled
+// into token-major LDS tiles by the global->LDS load path, two blocks in
+// flight, a barrier per phase.  The tiles' 16-byte columns are XOR-swizzled
 // by row so the operand reads are free of bank conflicts.  Each wavefront
 // computes S^T = K Q^T for its 32 queries with bf16 MFMA 32x32x16 (fp32
 // accumulate), runs the online softmax with one query column per lane (the
@@ -47,10 +47,7 @@ constexpr int TARGET_WGS = 256;   // one workgroup per CU
 #endif
 constexpr int BATCH_ROUNDS = OC_BATCH_ROUNDS;   // workgroups per CU a batched launch may queue
 constexpr float RESCALE_SLACK = 8.0f;   // log2 units the running max may lag
-#ifndef OC_LOOKAHEAD
-#define OC_LOOKAHEAD 4
-#endif
-constexpr int LOOKAHEAD = OC_LOOKAHEAD;   // MFMAs an operand read runs ahead of its use
+constexpr int LOOKAHEAD = 3;              // MFMAs an operand read runs ahead of its use
 
 struct KParams {
     const uint16_t *q;
@@ -322,9 +319,23 @@ __global__ __launch_bounds__(THREADS) void attn_fwd_kernel(KBatch batch) {
         klane[u] = (uint32_t)(r * D + ck * 8) * 2;
         vlane[u] = (uint32_t)(r * D + cv * 8) * 2;
     }
+    const uint32_t page_bytes = (uint32_t)(nkv * head_block * 2);     // one page of K (or V)
+    const int n_fast_pages = nkv * head_block * 2 <= 0xFFFFFFFFLL ? n_pre_pages : 0;
+    const unsigned char *const kg = reinterpret_cast<const unsigned char *>(pool_k + g * head_block);
+    const int64_t kv_step = (pool_v - pool_k) * 2;
     auto issue_block = [&](int b, int buf, const int32_t (&pid)[CPW]) {
         uint16_t *kt_lds = lds + buf * 2 * TILE;
         uint16_t *vt_lds = kt_lds + TILE;
+        if (b * 4 + 4 <= n_fast_pages) {     // all prefix: one 32 x 32 -> 64-bit product per page
+#pragma unroll
+            for (int u = 0; u < CPW; ++u) {
+                const int q = u * WAVES + wave;
+                const unsigned char *kp = kg + (uint64_t)(uint32_t)pid[u] * page_bytes;
+                dma16(kp, klane[u], kt_lds + q * 512);
+                dma16(kp + kv_step, vlane[u], vt_lds + q * 512);
+            }
+            return;
+        }
 #pragma unroll
         for (int u = 0; u < CPW; ++u) {
             const int q = u * WAVES + wave;                   // chunk index, uniform per wavefront
@@ -395,28 +406,47 @@ __global__ __launch_bounds__(THREADS) void attn_fwd_kernel(KBatch batch) {
     // (the second wavefront of every SIMD) run the same sequence one phase
     // later than wavefronts 0-3, so on every SIMD one wavefront's MFMAs run
     // beside the other's softmax.  A workgroup barrier ends every phase.
-    // Block j's tile becomes readable at phase 2j: its copies were started
-    // at phase 2j-4 and each wavefront waits for its own before the barrier;
-    // the copy of block j+2 then goes into the buffer of block j-2, whose
-    // last reads (wavefronts 4-7's PV of block j-2) ended with phase 2j-1.
+    //
+    // A wavefront issues its tile copies (scalar address work and vector
+    // memory instructions, some 400 cycles) at the start of a softmax phase:
+    // there they run in the shadow of the partner's MFMAs, while in a matrix
+    // phase the MFMA pipe would wait for them.  Block j+2's copies are thus
+    // issued in phase 2j by wavefronts 4-7 and in phase 2j+1 by wavefronts
+    // 0-3, into the buffer of block j-2, whose last reads (wavefronts 4-7's PV)
+    // ended with phase 2j-1; each wavefront waits for its own copies before
+    // the barrier that opens phase 2j+4, where the tile becomes readable.
+    // (65536 + 512 tokens, one layer: 507 us with both groups' copies at the
+    // barrier that opens a block, 490 like this; 553 with wavefronts 4-7's in
+    // their matrix phase; a fifth buffer with the copies one block further
+    // ahead changes nothing.)
     const bool first = (wave >> 2) == 0;
     auto tile_k = [&](int j) -> const uint16_t * { return lds + (j % NBUF) * 2 * TILE; };
     auto tile_v = [&](int j) -> const uint16_t * { return lds + (j % NBUF) * 2 * TILE + TILE; };
-    // phase 2j: block j's tile becomes readable, block j+2's copy starts
-    auto open_block = [&](int j) {
-        if (j + 1 < nb) wait_vmcnt<NDMA>();
-        else wait_vmcnt<0>();
-        lds_barrier();
+    auto refill = [&](int j) {
         if (j + 2 < nb) issue_block(b0 + j + 2, (j + 2) % NBUF, pid);
         if (j + 3 < nb) load_pids(b0 + j + 3, pid);
+    };
+    // The barrier that ends a matrix phase waits for the phase's tile reads
+    // (lds_barrier); the one that ends a softmax phase does not: the V^T
+    // fragments prefetched there may arrive after it, they are waited for
+    // where the matrix phase uses them.
+    auto softmax_end = [] { asm volatile("s_barrier" ::: "memory"); };
+    // this wavefront's copies of block j are in; the barrier that follows,
+    // the start of phase 2j, makes the tile readable
+    auto await_block = [&](int j) {
+        if (j + 1 < nb) wait_vmcnt<NDMA>();
+        else wait_vmcnt<0>();
+    };
+    // Wavefronts 4-7, in phase 2j: in the last, partial prefix page the slots
+    // past Tp may hold anything; zero them so masked keys contribute exactly
+    // nothing (the V tile is first read after the next barrier).
+    auto zero_stale = [&](int j) {
         const int b = b0 + j;
         if (j < nb && (b + 1) * 4 > full_pre_pages && b * 4 <= full_pre_pages && full_pre_pages < n_pre_pages) {
-            // last, partial prefix page: its slots past Tp may hold anything;
-            // zero them so masked keys contribute exactly nothing (the V
-            // tile is first read after the next barrier)
             uint16_t *V = lds + (j % NBUF) * 2 * TILE + TILE;
             const int pg = full_pre_pages - b * 4, k0 = Tp % PAGE;
-            for (int idx = tid; idx < D * (PAGE - k0); idx += THREADS) V[(pg * PAGE + k0) * D + idx] = 0;
+            for (int idx = tid - THREADS / 2; idx < D * (PAGE - k0); idx += THREADS / 2) V[(pg * PAGE + k0) * D + idx] = 0;
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         }
     };
     // A block needs the mask only if it holds slots of the prefix's partial
@@ -437,37 +467,45 @@ __global__ __launch_bounds__(THREADS) void attn_fwd_kernel(KBatch batch) {
     // the accumulators keep their registers); both execute the same barriers.
     if (nb > 0) {
         bf16x8 pre[LOOKAHEAD];
+        await_block(0);
+        lds_barrier();
         if (first) {
-            open_block(0);
             matrix_phase<D, false, true>(w, nullptr, voff, tile_k(0), qop, krow, half, pre);
             lds_barrier();
+            refill(0);
             softmax_block(0);
             for (int j = 1; j < nb; ++j) {
                 prefetch_vt<D>(tile_v(j - 1), voff, pre);
-                open_block(j);
+                await_block(j);
+                softmax_end();
                 matrix_phase<D, true, true>(w, tile_v(j - 1), voff, tile_k(j), qop, krow, half, pre);
                 lds_barrier();
+                refill(j);
                 softmax_block(j);
             }
             prefetch_vt<D>(tile_v(nb - 1), voff, pre);
-            open_block(nb);
+            softmax_end();
             matrix_phase<D, true, false>(w, tile_v(nb - 1), voff, nullptr, qop, krow, half, pre);
             lds_barrier();
         } else {
-            open_block(0);
+            refill(0);
+            zero_stale(0);
             lds_barrier();
             matrix_phase<D, false, true>(w, nullptr, voff, tile_k(0), qop, krow, half, pre);
             for (int j = 1; j < nb; ++j) {
-                open_block(j);
+                await_block(j);
+                lds_barrier();
+                refill(j);
+                zero_stale(j);
                 softmax_block(j - 1);
                 prefetch_vt<D>(tile_v(j - 1), voff, pre);
-                lds_barrier();
+                softmax_end();
                 matrix_phase<D, true, true>(w, tile_v(j - 1), voff, tile_k(j), qop, krow, half, pre);
             }
-            open_block(nb);
+            lds_barrier();
             softmax_block(nb - 1);
             prefetch_vt<D>(tile_v(nb - 1), voff, pre);
-            lds_barrier();
+            softmax_end();
             matrix_phase<D, true, false>(w, tile_v(nb - 1), voff, nullptr, qop, krow, half, pre);
         }
     }
@@ -976,7 +1014,7 @@ struct PlanCost {
     double wave;                // each further workgroup per CU
 };
 static const PlanCost COST_32 = {0.182, 0.112, 0.63, 4.2, 3.2, 1.4}, COST_64 = {0.259, 0.167, 1.38, 5.6, 3.5, 3.8},
-                      COST_256 = {1.49, 1.17, 0.88, 6.2, 1.6, 1.0};
+                      COST_256 = {1.45, 1.15, 0.88, 6.2, 1.6, 1.0};
 
 static double plan_cost(const AttnPlan &p) {
     const PlanCost &k = p.tile_rows == 32 ? COST_32 : p.tile_rows == 64 ? COST_64 : COST_256;
