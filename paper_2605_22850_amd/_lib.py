@@ -369,7 +369,7 @@ def oc_pipeline_run(ctx, requests: Sequence[Request], num_layers: int):
                 raise ValueError("chunk_objects must be C-contiguous")
             import numpy as np
             row = co.strides[0]
-            ptrs = co.ctypes.data + row * np.arange(co.shape[0], dtype=np.uint64)
+            ptrs = co.ctypes.data + row * np.arange(co.shape[0], dtype=np.int64)    # a single row's stride may be < 0
             objs = ctypes.cast(ptrs.ctypes.data, POINTER(c_void_p))
             keep.append(ptrs)
         creqs[i] = c_request(r.prefix_tokens, r.suffix_tokens, ctypes.pointer(bt), objs,

@@ -130,3 +130,21 @@ def test_errors_carry_the_library_message():
     with pytest.raises(oc.OcError) as e:
         oc.oc_kv_layer_ingest(Tensor(0x10), 4, Tensor(0x300, 9, 4), 128, Tensor(0x7000), LAY, 3, stream=0)
     assert e.value.status == _lib.OC_ERANGE and "layer out of range" in str(e.value)
+
+
+@pytest.mark.parametrize("rows", [slice(0, 3), slice(2, 3), slice(2, None, -3)])
+def test_chunk_object_pointers(rows, monkeypatch):
+    """One pointer per object; a single row counts as contiguous whatever its
+    stride, negative ones included."""
+    import numpy as np
+    objects = np.zeros((3, 64), np.int16)[rows]
+    n, seen = objects.shape[0], []
+
+    class Library:
+        def oc_pipeline_run(self, ctx, reqs, n_reqs, stats):
+            seen.extend(reqs[0].chunk_objects[j] for j in range(n))
+            return 0
+    monkeypatch.setattr(_lib, "lib", Library)
+    t = Tensor(0x10)
+    oc.oc_pipeline_run(None, [oc.Request(16 * n, 1, Tensor(0x300, 9, 4), t, t, t, t, chunk_objects=objects)], 1)
+    assert seen == [objects[j:].ctypes.data for j in range(n)]
