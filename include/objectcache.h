@@ -245,8 +245,8 @@ typedef struct {
 /* The chain above for one layer; attn_out is device bf16 [tokens][H] (the
  * attention output, as oc_suffix_prefill_layer writes it).  tokens == 0 is
  * not an error.  Asynchronous on `stream`; the library
- * keeps a 32 MiB workspace and a GEMM library handle per stream, each made by
- * the first call on that stream that needs it (which allocates). */
+ * keeps a 32 MiB workspace and a GEMM library handle per stream, both made by
+ * the first call on that stream (which allocates). */
 int oc_rest_of_layer(const void *attn_out, int64_t tokens, const oc_layout *layout,
                      const oc_layer_weights *weights, int32_t layer, const oc_layer_buffers *buffers,
                      void *stream);

@@ -40,9 +40,11 @@ __global__ __launch_bounds__(256) void silu_mul_kernel(const uint16_t *gu, uint1
 }
 
 // Per (device, stream): a rocBLAS handle and the few-row GEMM's workspace,
-// each made when first needed; neither may be shared by GEMMs running on
-// different streams.  They live until the process ends, or until
-// forget_blas_stream() for streams the library owns.
+// both made by the first call on the stream, whichever of them its row count
+// needs, so that any later call on it, under capture too, allocates neither.
+// They may not be shared by GEMMs running on different streams.  They live
+// until the process ends, or until forget_blas_stream() for streams the
+// library owns.
 struct StreamState {
     rocblas_handle handle = nullptr;
     void *ws = nullptr;
@@ -53,16 +55,18 @@ static std::map<std::pair<int, hipStream_t>, StreamState> g_blas;
 static int stream_state(hipStream_t s, StreamState **out) {
     int dev = 0;
     OC_HIP(hipGetDevice(&dev));
-    *out = &g_blas[std::make_pair(dev, s)];
-    return OC_OK;
-}
-
-static int blas_for(StreamState *st, hipStream_t s) {
+    StreamState *st = &g_blas[std::make_pair(dev, s)];
     if (!st->handle && rocblas_create_handle(&st->handle) != rocblas_status_success) {
         st->handle = nullptr;
         return fail(OC_EHIP, "rocblas_create_handle failed");
     }
     if (rocblas_set_stream(st->handle, s) != rocblas_status_success) return fail(OC_EHIP, "rocblas_set_stream failed");
+    // without memory for the workspace every product goes to the library
+    if (!st->ws && hipMalloc(&st->ws, GEMM_WORKSPACE_BYTES) != hipSuccess) {
+        (void)hipGetLastError();
+        st->ws = nullptr;
+    }
+    *out = st;
     return OC_OK;
 }
 
@@ -106,19 +110,12 @@ int launch_rest_of_layer(const LayerArgs &a, hipStream_t s) {
     // one product of the chain on m rows; with `act`, the gating as well
     auto product = [&](const uint16_t *x, const uint16_t *w, uint16_t *y, uint16_t *act, int64_t m, int64_t K,
                        int64_t N) -> int {
-        if (gemm_rows_applies(m, K, N)) {
-            // without memory for its workspace the product goes to the library
-            if (!st->ws && hipMalloc(&st->ws, GEMM_WORKSPACE_BYTES) != hipSuccess) {
-                (void)hipGetLastError();
-                st->ws = nullptr;
-            }
-            if (st->ws) {
-                OC_HIP(launch_gemm_rows(x, w, y, act, st->ws, m, K, N, s));
-                return OC_OK;
-            }
+        if (st->ws && gemm_rows_applies(m, K, N)) {
+            OC_HIP(launch_gemm_rows(x, w, y, act, st->ws, m, K, N, s));
+            return OC_OK;
         }
-        int r = blas_for(st, s);
-        if (r || (r = gemm(st->handle, x, w, y, m, K, N))) return r;
+        const int r = gemm(st->handle, x, w, y, m, K, N);
+        if (r) return r;
         if (act) {
             const int64_t n = m * (N / 16);
             hipLaunchKernelGGL(silu_mul_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, y, act,

@@ -125,3 +125,25 @@ def test_under_capture():
         torch.cuda.synchronize()
         assert all(torch.equal(a, b) for a, b in zip(c.bufs, want)), f"replay {k}"
         c.check(f"replay {k}")
+
+
+def test_captured_on_a_stream_warmed_with_other_rows():
+    """The first call on a stream makes all that later calls on it need: 1024
+    rows (the GEMM library's), then 130 (this library's kernels) captured."""
+    import torch
+    print("[gemm rows] warmed with 1024 rows, captured with 130", flush=True)
+    big, c = Layer(8, 2, 64, 1792, 1024, seed=10), Layer(8, 2, 64, 1792, 130, seed=11)
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        big.run(s)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s):
+        c.run(s)
+    for k in range(3):
+        for b in c.bufs:
+            b[:c.T].fill_(float(k))
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        c.check(f"replay {k}")
