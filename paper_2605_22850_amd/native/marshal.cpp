@@ -24,17 +24,16 @@ decltype(&oc_suffix_prefill_layer) f_attention;
 decltype(&oc_suffix_prefill_layer_noalloc) f_attention_noalloc;
 decltype(&oc_rest_of_layer) f_rest;
 
-PyObject *s_data_ptr, *s_numel, *s_element_size, *s_cuda_stream;
+PyObject *s_data_ptr, *s_numel, *s_element_size, *s_cuda_stream, *s_value;
 PyObject *s_layout[7];                        // Layout's fields, in the struct's order
 PyObject *s_weights[5];                       // LayerWeights' fields
+PyObject *t_c_void_p;                         // ctypes.c_void_p
 PyObject *g_current_stream;                   // () -> the current stream's handle
 
-// An int, as ctypes takes one: anything else is a TypeError; wider values wrap.
+// An integer, as ctypes takes one: an int or what has __index__ (NumPy
+// integers, integer tensors of one element), else a TypeError; wider values
+// wrap.
 bool as_i64(PyObject *o, int64_t *out) {
-    if (!PyLong_Check(o)) {
-        PyErr_Format(PyExc_TypeError, "int expected instead of %.100s", Py_TYPE(o)->tp_name);
-        return false;
-    }
     *out = (int64_t)PyLong_AsUnsignedLongLongMask(o);
     return !PyErr_Occurred();
 }
@@ -53,14 +52,39 @@ bool call_int(PyObject *o, PyObject *method, int64_t *out) {
     return ok;
 }
 
+// An address, as ctypes takes one: an int, None or a c_void_p; an object that
+// merely has __index__ is a TypeError.
+bool as_address(PyObject *o, void **out) {
+    *out = nullptr;
+    if (o == Py_None) return true;
+    if (PyLong_Check(o)) {
+        *out = reinterpret_cast<void *>(PyLong_AsUnsignedLongLongMask(o));
+        return !PyErr_Occurred();
+    }
+    const int is = PyObject_IsInstance(o, t_c_void_p);
+    if (is < 0) return false;
+    if (!is) {
+        PyErr_Format(PyExc_TypeError, "%.100s cannot be converted to pointer", Py_TYPE(o)->tp_name);
+        return false;
+    }
+    PyObject *v = PyObject_GetAttr(o, s_value);      // None or an int
+    if (!v) return false;
+    if (v != Py_None) *out = reinterpret_cast<void *>(PyLong_AsUnsignedLongLongMask(v));
+    Py_DECREF(v);
+    return !PyErr_Occurred();
+}
+
 template <class T>
 bool as_ptr(PyObject *tensor, T **out) {      // None: NULL
     *out = nullptr;
     if (tensor == Py_None) return true;
-    int64_t v;
-    if (!call_int(tensor, s_data_ptr, &v)) return false;
-    *out = reinterpret_cast<T *>(v);
-    return true;
+    PyObject *r = PyObject_CallMethodNoArgs(tensor, s_data_ptr);
+    if (!r) return false;
+    void *v;
+    const bool ok = as_address(r, &v);
+    Py_DECREF(r);
+    *out = static_cast<T *>(v);
+    return ok;
 }
 
 bool as_layout(PyObject *o, oc_layout *l) {
@@ -96,10 +120,8 @@ bool as_stream(PyObject *o, void **out) {     // None: the current torch stream
     else if (PyLong_Check(o)) v = Py_NewRef(o);
     else v = PyObject_GetAttr(o, s_cuda_stream);
     if (!v) return false;
-    int64_t h = 0;
-    const bool ok = v == Py_None || as_i64(v, &h);
+    const bool ok = as_address(v, out);
     Py_DECREF(v);
-    *out = reinterpret_cast<void *>(h);
     return ok;
 }
 
@@ -290,8 +312,13 @@ PyMODINIT_FUNC PyInit__marshal() {
                                           "page_size",  "chunk_tokens", "num_pages"};
     static const char *const weights[5] = {"ffn_dim", "w_o", "w_gate_up", "w_down", "w_qkv"};
     if (!intern(&s_data_ptr, "data_ptr") || !intern(&s_numel, "numel") || !intern(&s_element_size, "element_size") ||
-        !intern(&s_cuda_stream, "cuda_stream"))
+        !intern(&s_cuda_stream, "cuda_stream") || !intern(&s_value, "value"))
         return nullptr;
+    PyObject *ctypes = PyImport_ImportModule("ctypes");
+    if (!ctypes) return nullptr;
+    t_c_void_p = PyObject_GetAttrString(ctypes, "c_void_p");
+    Py_DECREF(ctypes);
+    if (!t_c_void_p) return nullptr;
     for (int i = 0; i < 7; ++i)
         if (!intern(&s_layout[i], layout[i])) return nullptr;
     for (int i = 0; i < 5; ++i)

@@ -126,6 +126,66 @@ def test_refused_arguments(calls):
     assert calls == []
 
 
+def test_integers_that_are_no_int(calls):
+    """Counts and layout fields are taken as ctypes takes them: whatever has
+    __index__, such as a NumPy integer or an integer tensor of one element."""
+    import numpy as np
+    import torch
+    t, pages, pool = Tensor, Tensor(0x300, np.int64(9), 4), Tensor(0x7000)
+    for num in (np.int32, np.int64, lambda v: np.array([v])[0], torch.tensor, lambda v: torch.tensor([v])):
+        lay = oc.Layout(*(num(f) for f in (3, 8, 2, 64, 16, 32, 1 << 20)))
+        lay_c = dict(LAY_C, num_pages=1 << 20)
+        p = {"base": 0x7000, "layout": lay_c}
+        st = {"data": 0x10, "num_chunks": 4, "per_layer_chunk_bytes": S}
+        calls.clear()
+        oc.oc_kv_layer_ingest(t(0x10), num(4), pages, num(130), pool, lay, num(2))
+        oc.oc_kv_chunks_ingest(t(0x10), num(4), num(5), pages, num(130), pool, lay)
+        oc.oc_kv_layer_gather(pages, num(130), pool, lay, num(1), t(0x12), num(4))
+        oc.oc_kv_chunks_gather(pages, num(130), pool, lay, num(6), num(7), t(0x13))
+        oc.oc_kv_suffix_append(t(0x14), t(0x15), num(21), pages, num(130), pool, lay, num(2))
+        oc.oc_suffix_prefill_layer(t(1), t(2), t(3), num(21), pool, lay, pages, num(130), num(2), t(4), t(5, 100, 4))
+        oc.oc_suffix_prefill_layer_noalloc(t(1), t(2), t(3), num(21), pool, lay, pages, num(130), num(2), t(4))
+        w = oc.LayerWeights(num(48), t(0x20), t(0x21), t(0x22), t(0x23))
+        oc.oc_rest_of_layer(t(6), num(21), lay, w, num(1), t(7), t(8), t(9), t(10), t(11))
+        cur = 0x5150
+        assert calls == [
+            ("oc_kv_layer_ingest", [st, TABLE, p, 2, cur]),
+            ("oc_kv_chunks_ingest", [st, 5, TABLE, p, cur]),
+            ("oc_kv_layer_gather", [TABLE, p, 1, 0x12, 4, S, cur]),
+            ("oc_kv_chunks_gather", [TABLE, p, 6, 7, 0x13, cur]),
+            ("oc_kv_suffix_append", [0x14, 0x15, 21, TABLE, p, 2, cur]),
+            ("oc_suffix_prefill_layer", [1, 2, 3, 21, p, TABLE, 2, 4, 5, 400, cur]),
+            ("oc_suffix_prefill_layer_noalloc", [1, 2, 3, 21, p, TABLE, 2, 4, cur]),
+            ("oc_rest_of_layer", [6, 21, lay_c, {"ffn_dim": 48, "w_o": 0x20, "w_gate_up": 0x21, "w_down": 0x22,
+                                                 "w_qkv": 0x23}, 1,
+                                  {"o": 7, "gate_up": 8, "act": 9, "h": 10, "qkv": 11}, cur]),
+        ]
+
+
+def test_addresses(calls):
+    """Pointers and stream handles: an int, None or a c_void_p; a NumPy integer
+    is no address."""
+    import numpy as np
+
+    class Handle:
+        def __init__(self, h):
+            self.cuda_stream = h
+    pages, pool = Tensor(0x300, 9, 4), Tensor(0x7000)
+    for h, want in ((0x99, 0x99), (None, None), (0, None), (c_void_p(0x98), 0x98), (c_void_p(), None)):
+        calls.clear()
+        oc.oc_kv_layer_ingest(Tensor(0x10), 4, pages, 130, pool, LAY, 2, stream=Handle(h))
+        assert calls[0][1][4] == want
+    calls.clear()
+    oc.oc_kv_layer_ingest(Tensor(c_void_p(0x10)), 4, pages, 130, Tensor(c_void_p()), LAY, 2)
+    assert calls[0][1][0]["data"] == 0x10 and calls[0][1][2]["base"] is None
+    calls.clear()
+    with pytest.raises(TypeError):
+        oc.oc_kv_layer_ingest(Tensor(0x10), 4, pages, 130, pool, LAY, 2, stream=Handle(np.int64(5)))
+    with pytest.raises(TypeError):
+        oc.oc_kv_layer_ingest(Tensor(np.int64(0x10)), 4, pages, 130, pool, LAY, 2)
+    assert calls == []
+
+
 def test_errors_carry_the_library_message():
     with pytest.raises(oc.OcError) as e:
         oc.oc_kv_layer_ingest(Tensor(0x10), 4, Tensor(0x300, 9, 4), 128, Tensor(0x7000), LAY, 3, stream=0)
