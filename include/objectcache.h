@@ -244,9 +244,16 @@ typedef struct {
 
 /* The chain above for one layer; attn_out is device bf16 [tokens][H] (the
  * attention output, as oc_suffix_prefill_layer writes it).  tokens == 0 is
- * not an error.  Asynchronous on `stream`; the library
- * keeps a 32 MiB workspace and a GEMM library handle per stream, both made by
- * the first call on that stream (which allocates). */
+ * not an error.  Asynchronous on `stream`.  The library keeps a GEMM library
+ * handle per stream and, for the partial sums of products whose K it splits, a
+ * 32 MiB workspace; the first eager call on a stream makes both (it allocates;
+ * later calls on that stream do not, under capture or not).  Calls under
+ * stream capture and on hipStreamPerThread use no such workspace, since their
+ * kernels may run beside other calls' on the same stream handle: graphs
+ * captured on one stream may be replayed together, on any streams.  Their
+ * split products go to the GEMM library instead, with the same rounding
+ * points, so a captured call and an eager one may differ in the order of fp32
+ * sums.  A stream's calls must have finished before it is destroyed. */
 int oc_rest_of_layer(const void *attn_out, int64_t tokens, const oc_layout *layout,
                      const oc_layer_weights *weights, int32_t layer, const oc_layer_buffers *buffers,
                      void *stream);

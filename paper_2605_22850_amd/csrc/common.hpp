@@ -133,9 +133,12 @@ void forget_blas_stream(hipStream_t s);
 // y[M][N] = x[M][K] . w[K][N], bf16 row-major, 16-byte aligned; with `act`,
 // also act[M][N/2] = silu(y[:, :N/2]) * y[:, N/2:].  `ws` holds split
 // partials, GEMM_WORKSPACE_BYTES of device memory that nothing else uses
-// while the call runs.
+// while the call's kernels run; NULL only where the product is not split.
 constexpr size_t GEMM_WORKSPACE_BYTES = (size_t)32 << 20;
-bool gemm_rows_applies(int64_t M, int64_t K, int64_t N);
+// whether these kernels take the product, with and without a workspace
+bool gemm_rows_applies(int64_t M, int64_t K, int64_t N, bool has_workspace);
+// ranges that K is split into
+int64_t gemm_rows_splits(int64_t M, int64_t K, int64_t N);
 hipError_t launch_gemm_rows(const uint16_t *x, const uint16_t *w, uint16_t *y, uint16_t *act, void *ws, int64_t M,
                             int64_t K, int64_t N, hipStream_t s);
 

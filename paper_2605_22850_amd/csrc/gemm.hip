@@ -275,23 +275,38 @@ static int rows_per_tile(int64_t M) {
     return (M + 127) / 128 % 2 && M > 256 ? 128 : 256;
 }
 
+// Tiles of one product and the ranges its K is split into.
+struct RowsPlan {
+    int64_t bm, m_tiles, n_tiles, n_split, steps_per_split;
+};
+static RowsPlan plan_rows(int64_t M, int64_t K, int64_t N) {
+    RowsPlan r;
+    r.bm = rows_per_tile(M);
+    r.m_tiles = (M + r.bm - 1) / r.bm;
+    r.n_tiles = N / GEMM_BN;
+    // one workgroup per CU; at least four steps each, so that the ring fills;
+    // within the workspace
+    const int64_t tiles = r.m_tiles * r.n_tiles, steps = K / BK;
+    int64_t split = std::min<int64_t>(GEMM_WGS / tiles, steps / 4);
+    split = std::min<int64_t>(split, (int64_t)GEMM_WORKSPACE_BYTES / (tiles * r.bm * GEMM_BN * 4));
+    if (split < 1) split = 1;
+    r.steps_per_split = (steps + split - 1) / split;
+    r.n_split = (steps + r.steps_per_split - 1) / r.steps_per_split;
+    return r;
+}
+
 template <int WM, int WN, int MW, int NW, int NS, bool GLU>
-static hipError_t launch_shape(GemmParams p, hipStream_t s) {
+static hipError_t launch_shape(GemmParams p, const RowsPlan &r, hipStream_t s) {
     using Sh = GemmShape<WM, WN, MW, NW>;
     static_assert(Sh::BN == GEMM_BN, "column tile");
     constexpr size_t lds = (size_t)NS * Sh::STEP * 2;
     static_assert(lds <= CU_LDS_BYTES, "ring larger than the LDS");
-    p.m_tiles = (p.M + Sh::BM - 1) / Sh::BM;
-    p.n_tiles = p.N / Sh::BN;
-    // one workgroup per CU; at least four steps each, so that the ring fills;
-    // within the workspace
-    const int64_t tiles = (int64_t)p.m_tiles * p.n_tiles;
-    const int steps = p.K / BK;
-    int64_t split = std::min<int64_t>(GEMM_WGS / tiles, steps / 4);
-    split = std::min<int64_t>(split, (int64_t)GEMM_WORKSPACE_BYTES / (tiles * Sh::TILE * 4));
-    if (split < 1) split = 1;
-    p.steps_per_split = (int)((steps + split - 1) / split);
-    p.n_split = (steps + p.steps_per_split - 1) / p.steps_per_split;
+    if (r.bm != Sh::BM || (r.n_split > 1 && !p.part)) return hipErrorInvalidValue;
+    p.m_tiles = (int32_t)r.m_tiles;
+    p.n_tiles = (int32_t)r.n_tiles;
+    p.n_split = (int32_t)r.n_split;
+    p.steps_per_split = (int32_t)r.steps_per_split;
+    const int64_t tiles = r.m_tiles * r.n_tiles;
     const hipError_t e = allow_dynamic_lds<&gemm_rows_kernel<WM, WN, MW, NW, NS, GLU>>((int)lds);
     if (e != hipSuccess) return e;
     const int64_t grid = 8LL * ((p.n_tiles * p.n_split + 7) / 8) * p.m_tiles;
@@ -304,12 +319,12 @@ static hipError_t launch_shape(GemmParams p, hipStream_t s) {
 }
 
 template <bool GLU>
-static hipError_t launch_glu(const GemmParams &p, hipStream_t s) {
-    switch (rows_per_tile(p.M)) {
-        case 32: return launch_shape<1, 4, 1, 1, 4, GLU>(p, s);
-        case 64: return launch_shape<1, 4, 2, 1, 3, GLU>(p, s);
-        case 128: return launch_shape<2, 2, 2, 2, 4, GLU>(p, s);
-        default: return launch_shape<2, 4, 4, 1, 3, GLU>(p, s);
+static hipError_t launch_glu(const GemmParams &p, const RowsPlan &r, hipStream_t s) {
+    switch (r.bm) {
+        case 32: return launch_shape<1, 4, 1, 1, 4, GLU>(p, r, s);
+        case 64: return launch_shape<1, 4, 2, 1, 3, GLU>(p, r, s);
+        case 128: return launch_shape<2, 2, 2, 2, 4, GLU>(p, r, s);
+        default: return launch_shape<2, 4, 4, 1, 3, GLU>(p, r, s);
     }
 }
 
@@ -324,13 +339,17 @@ static hipError_t launch_glu(const GemmParams &p, hipStream_t s) {
 //    library's product): 47/59 at 1 row, 47/50 at 32, 52/52 at 64, then 62/57
 //    at 96 and 92/72 at 160: X moves through each CU once per column tile,
 //    and past 64 rows that costs more than the fused gating saves.
-bool gemm_rows_applies(int64_t M, int64_t K, int64_t N) {
+// Without a workspace a product whose K would be split is the library's.
+bool gemm_rows_applies(int64_t M, int64_t K, int64_t N, bool has_workspace) {
     if (M < 1 || K < BK || K % BK || N % GEMM_BN || N < GEMM_BN) return false;
     // 32-bit offsets within a step's rows of W and a row tile of X
     if ((int64_t)BK * N * 2 >= INT32_MAX || 256 * K * 2 >= INT32_MAX) return false;
-    const int64_t bm = rows_per_tile(M), tiles = (M + bm - 1) / bm * (N / GEMM_BN);
-    return M <= 64 || (M <= 512 && tiles * 2 <= GEMM_WGS);
+    const RowsPlan r = plan_rows(M, K, N);
+    if (M > 64 && (M > 512 || r.m_tiles * r.n_tiles * 2 > GEMM_WGS)) return false;
+    return has_workspace || r.n_split == 1;
 }
+
+int64_t gemm_rows_splits(int64_t M, int64_t K, int64_t N) { return plan_rows(M, K, N).n_split; }
 
 hipError_t launch_gemm_rows(const uint16_t *x, const uint16_t *w, uint16_t *y, uint16_t *act, void *ws, int64_t M,
                             int64_t K, int64_t N, hipStream_t s) {
@@ -343,7 +362,8 @@ hipError_t launch_gemm_rows(const uint16_t *x, const uint16_t *w, uint16_t *y, u
     p.M = (int32_t)M;
     p.N = (int32_t)N;
     p.K = (int32_t)K;
-    return act ? launch_glu<true>(p, s) : launch_glu<false>(p, s);
+    const RowsPlan r = plan_rows(M, K, N);
+    return act ? launch_glu<true>(p, r, s) : launch_glu<false>(p, r, s);
 }
 
 }  // namespace oc

@@ -39,12 +39,16 @@ __global__ __launch_bounds__(256) void silu_mul_kernel(const uint16_t *gu, uint1
     *reinterpret_cast<u32x4 *>(act + t * 8 * F8 + c * 8) = __builtin_bit_cast(u32x4, __builtin_convertvector(r, bf16x8));
 }
 
-// Per (device, stream): a rocBLAS handle and the few-row GEMM's workspace,
-// both made by the first call on the stream, whichever of them its row count
-// needs, so that any later call on it, under capture too, allocates neither.
-// They may not be shared by GEMMs running on different streams.  They live
-// until the process ends, or until forget_blas_stream() for streams the
-// library owns.
+// Per (device, stream): a rocBLAS handle and the few-row GEMM's workspace for
+// split partials, both made by the first eager call on the stream, whichever of
+// them its row count needs.  They live until the process ends, or until
+// forget_blas_stream() for streams the library owns.
+//
+// The workspace serves one call at a time because calls on one stream run in
+// order.  That does not hold for a captured call (its graph may be replayed on
+// any stream, beside other graphs captured on this one and beside eager calls)
+// nor for hipStreamPerThread (one handle, a queue per host thread): these get
+// no workspace, and products that would need one go to the GEMM library.
 struct StreamState {
     rocblas_handle handle = nullptr;
     void *ws = nullptr;
@@ -52,7 +56,15 @@ struct StreamState {
 static std::mutex g_blas_mu;
 static std::map<std::pair<int, hipStream_t>, StreamState> g_blas;
 
-static int stream_state(hipStream_t s, StreamState **out) {
+static bool capturing(hipStream_t s) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();      // the null stream while another captures: the launches report it
+    return false;
+}
+
+// the stream's handle, and the workspace that this call may use (or NULL)
+static int stream_state(hipStream_t s, rocblas_handle *handle, void **ws) {
     int dev = 0;
     OC_HIP(hipGetDevice(&dev));
     StreamState *st = &g_blas[std::make_pair(dev, s)];
@@ -61,12 +73,15 @@ static int stream_state(hipStream_t s, StreamState **out) {
         return fail(OC_EHIP, "rocblas_create_handle failed");
     }
     if (rocblas_set_stream(st->handle, s) != rocblas_status_success) return fail(OC_EHIP, "rocblas_set_stream failed");
-    // without memory for the workspace every product goes to the library
+    *handle = st->handle;
+    *ws = nullptr;
+    if (s == hipStreamPerThread || capturing(s)) return OC_OK;
+    // without memory for the workspace the products that need it go to the library
     if (!st->ws && hipMalloc(&st->ws, GEMM_WORKSPACE_BYTES) != hipSuccess) {
         (void)hipGetLastError();
         st->ws = nullptr;
     }
-    *out = st;
+    *ws = st->ws;
     return OC_OK;
 }
 
@@ -102,19 +117,20 @@ static int gemm(rocblas_handle h, const uint16_t *X, const uint16_t *W, uint16_t
 int launch_rest_of_layer(const LayerArgs &a, hipStream_t s) {
     if (a.T == 0) return OC_OK;
     std::lock_guard<std::mutex> g(g_blas_mu);
-    StreamState *st = nullptr;
-    int rc = stream_state(s, &st);
+    rocblas_handle handle = nullptr;
+    void *ws = nullptr;
+    int rc = stream_state(s, &handle, &ws);
     if (rc) return rc;
     const int64_t widest = std::max(std::max(2 * a.F, a.H), a.NQKV);
     const int64_t rb = std::max<int64_t>(1, (INT64_C(1) << 29) / widest);
     // one product of the chain on m rows; with `act`, the gating as well
     auto product = [&](const uint16_t *x, const uint16_t *w, uint16_t *y, uint16_t *act, int64_t m, int64_t K,
                        int64_t N) -> int {
-        if (st->ws && gemm_rows_applies(m, K, N)) {
-            OC_HIP(launch_gemm_rows(x, w, y, act, st->ws, m, K, N, s));
+        if (gemm_rows_applies(m, K, N, ws != nullptr)) {
+            OC_HIP(launch_gemm_rows(x, w, y, act, ws, m, K, N, s));
             return OC_OK;
         }
-        const int r = gemm(st->handle, x, w, y, m, K, N);
+        const int r = gemm(handle, x, w, y, m, K, N);
         if (r) return r;
         if (act) {
             const int64_t n = m * (N / 16);

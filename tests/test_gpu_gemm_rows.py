@@ -1,7 +1,9 @@
 """The few-row GEMM kernels behind oc_rest_of_layer, stage by stage against
 float64 products of the same bfloat16 inputs, at the edges of their row
 tiles, K splits and of the rule that hands products to the GEMM library; on
-several streams and under capture."""
+several streams, under capture, and where one stream handle's calls overlap."""
+import threading
+
 import pytest
 
 from tests.gpu_util import require_gpu
@@ -113,18 +115,101 @@ def test_under_capture():
     with torch.cuda.stream(s):
         c.run(s)            # the stream's workspace is made before the capture
     torch.cuda.synchronize()
-    want = [b.clone() for b in c.bufs]
     g = torch.cuda.CUDAGraph()
     with torch.cuda.graph(g, stream=s):
         c.run(s)
+    # a captured call has no split partials, so its sums may differ from the
+    # eager call's in order; every replay repeats the first bit for bit
+    want = None
     for k in range(4):
         for b in c.bufs:
             b[:c.T].fill_(float(k))
         torch.cuda.synchronize()
         g.replay()
         torch.cuda.synchronize()
+        if want is None:
+            want = [b.clone() for b in c.bufs]
         assert all(torch.equal(a, b) for a, b in zip(c.bufs, want)), f"replay {k}"
         c.check(f"replay {k}")
+
+
+def test_unsplit_products_under_capture_equal_eager():
+    # K of 4 steps at most (H 256, F 256): no product is split, so the captured
+    # call runs the same kernels as the eager one
+    import torch
+    print("[gemm rows] captured, no splits", flush=True)
+    c = Layer(4, 1, 64, 256, 40, seed=12)
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        c.run(s)
+    torch.cuda.synchronize()
+    want = [b.clone() for b in c.bufs]
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s):
+        c.run(s)
+    for k in range(3):
+        for b in c.bufs:
+            b[:c.T].fill_(float(k))
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(c.bufs, want)), f"replay {k}"
+
+
+def test_graphs_of_one_stream_replayed_together():
+    """Two graphs captured on one stream, replayed on two others beside eager
+    calls on it: no call's kernels may use another's partial sums."""
+    import torch
+    print("[gemm rows] two graphs of one stream and eager calls, overlapping", flush=True)
+    a, b, c = (Layer(32, 8, 128, 2048, t, seed=70 + t) for t in (40, 130, 60))
+    s, s1, s2 = (torch.cuda.Stream() for _ in range(3))
+    with torch.cuda.stream(s):
+        c.run(s)
+    torch.cuda.synchronize()
+    graphs = []
+    for x in (a, b):
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=s):
+            x.run(s)
+        graphs.append(g)
+    torch.cuda.synchronize()
+    for k in range(4):
+        for _ in range(5):
+            with torch.cuda.stream(s1):
+                graphs[0].replay()
+            with torch.cuda.stream(s2):
+                graphs[1].replay()
+            c.run(s)
+        torch.cuda.synchronize()
+        for x, what in ((a, "first graph"), (b, "second graph"), (c, "eager")):
+            x.check(f"round {k}, {what}")
+
+
+def test_threads_on_the_per_thread_stream():
+    """hipStreamPerThread is one handle for a stream per host thread."""
+    import torch
+    print("[gemm rows] two threads on the per-thread stream", flush=True)
+    cases = [Layer(32, 8, 128, 2048, t, seed=80 + t) for t in (40, 130)]
+    torch.cuda.synchronize()
+    start, errors = threading.Barrier(2), []
+
+    def work(c):
+        try:
+            start.wait(30)
+            for _ in range(10):
+                c.run(stream=2)               # hipStreamPerThread
+            torch.cuda.synchronize()
+        except Exception as e:                # reported by the main thread
+            errors.append(e)
+    threads = [threading.Thread(target=work, args=(c,)) for c in cases]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    assert not errors, errors
+    for i, c in enumerate(cases):
+        c.check(f"thread {i}")
 
 
 def test_captured_on_a_stream_warmed_with_other_rows():
