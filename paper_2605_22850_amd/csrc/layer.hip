@@ -12,6 +12,7 @@
 #include <utility>
 
 #include "common.hpp"
+#include "split_workspace.hpp"
 
 namespace oc {
 
@@ -51,7 +52,7 @@ __global__ __launch_bounds__(256) void silu_mul_kernel(const uint16_t *gu, uint1
 // no workspace, and products that would need one go to the GEMM library.
 struct StreamState {
     rocblas_handle handle = nullptr;
-    void *ws = nullptr;
+    SplitWorkspace ws;
 };
 static std::mutex g_blas_mu;
 static std::map<std::pair<int, hipStream_t>, StreamState> g_blas;
@@ -76,12 +77,12 @@ static int stream_state(hipStream_t s, rocblas_handle *handle, void **ws) {
     *handle = st->handle;
     *ws = nullptr;
     if (s == hipStreamPerThread || capturing(s)) return OC_OK;
-    // without memory for the workspace the products that need it go to the library
-    if (!st->ws && hipMalloc(&st->ws, GEMM_WORKSPACE_BYTES) != hipSuccess) {
+    *ws = st->ws.get([] {
+        void *p = nullptr;
+        if (hipMalloc(&p, GEMM_WORKSPACE_BYTES) == hipSuccess) return p;
         (void)hipGetLastError();
-        st->ws = nullptr;
-    }
-    *ws = st->ws;
+        return (void *)nullptr;
+    });
     return OC_OK;
 }
 
@@ -90,7 +91,7 @@ void forget_blas_stream(hipStream_t s) {
     for (auto it = g_blas.begin(); it != g_blas.end();) {
         if (it->first.second == s) {
             if (it->second.handle) rocblas_destroy_handle(it->second.handle);
-            if (it->second.ws) (void)hipFree(it->second.ws);
+            if (it->second.ws.ptr) (void)hipFree(it->second.ws.ptr);
             it = g_blas.erase(it);
         } else {
             ++it;
