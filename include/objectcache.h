@@ -22,8 +22,9 @@
  *     oc_last_error() returns a message (thread-local, valid until the next
  *     call on the same thread).  No C++ exception crosses this boundary.
  *   - The library never allocates device memory inside the single-layer
- *     calls; scratch space is the caller's `workspace` (or, for
- *     oc_suffix_prefill_layer_noalloc, a static device array).
+ *     calls (except in the first oc_rest_of_layer on a stream); scratch space
+ *     is the caller's `workspace` (or, for oc_suffix_prefill_layer_noalloc, a
+ *     static device array).
  *   - Lengths are validated against the kernels' 32-bit index arithmetic as
  *     well: a shape whose offsets, rows or grid would not fit is OC_ERANGE.
  */
@@ -246,14 +247,14 @@ typedef struct {
  * attention output, as oc_suffix_prefill_layer writes it).  tokens == 0 is
  * not an error.  Asynchronous on `stream`.  The library keeps a GEMM library
  * handle per stream and, for the partial sums of products whose K it splits, a
- * 32 MiB workspace; the first eager call on a stream makes both (it allocates;
- * later calls on that stream do not, under capture or not).  Calls under
- * stream capture and on hipStreamPerThread use no such workspace, since their
- * kernels may run beside other calls' on the same stream handle: graphs
- * captured on one stream may be replayed together, on any streams.  Their
- * split products go to the GEMM library instead, with the same rounding
- * points, so a captured call and an eager one may differ in the order of fp32
- * sums.  A stream's calls must have finished before it is destroyed. */
+ * 32 MiB workspace (at most 64 of these in a process); the first eager call on
+ * a stream makes both (it allocates; later calls on that stream do not, under
+ * capture or not).  Calls under stream capture and on hipStreamPerThread use no
+ * workspace, since their kernels may run beside other calls' on the same stream
+ * handle: graphs captured on one stream may be replayed together, on any
+ * streams.  Without a workspace, products that would be split go to the GEMM
+ * library, with the same rounding points but another order of fp32 sums.
+ * A stream's calls must have finished before it is destroyed. */
 int oc_rest_of_layer(const void *attn_out, int64_t tokens, const oc_layout *layout,
                      const oc_layer_weights *weights, int32_t layer, const oc_layer_buffers *buffers,
                      void *stream);

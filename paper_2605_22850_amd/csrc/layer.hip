@@ -56,6 +56,7 @@ struct StreamState {
 };
 static std::mutex g_blas_mu;
 static std::map<std::pair<int, hipStream_t>, StreamState> g_blas;
+static int g_workspaces = 0;
 
 static bool capturing(hipStream_t s) {
     hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
@@ -77,7 +78,7 @@ static int stream_state(hipStream_t s, rocblas_handle *handle, void **ws) {
     *handle = st->handle;
     *ws = nullptr;
     if (s == hipStreamPerThread || capturing(s)) return OC_OK;
-    *ws = st->ws.get([] {
+    *ws = st->ws.get(g_workspaces, [] {
         void *p = nullptr;
         if (hipMalloc(&p, GEMM_WORKSPACE_BYTES) == hipSuccess) return p;
         (void)hipGetLastError();
@@ -91,7 +92,7 @@ void forget_blas_stream(hipStream_t s) {
     for (auto it = g_blas.begin(); it != g_blas.end();) {
         if (it->first.second == s) {
             if (it->second.handle) rocblas_destroy_handle(it->second.handle);
-            if (it->second.ws.ptr) (void)hipFree(it->second.ws.ptr);
+            it->second.ws.give_back(g_workspaces, [](void *p) { (void)hipFree(p); });
             it = g_blas.erase(it);
         } else {
             ++it;

@@ -1,4 +1,4 @@
-"""The bookkeeping of a stream's split workspace, compiled for the host alone
+"""The bookkeeping of the streams' split workspaces, compiled for the host alone
 with an allocator that refuses."""
 import os
 import subprocess
@@ -12,21 +12,30 @@ PROGRAM = r"""
 #define CHECK(x) do { if (!(x)) { std::printf("line %d: %s\n", __LINE__, #x); return 1; } } while (0)
 
 int main() {
-    int calls = 0, memory = 0;
+    int calls = 0, memory = 0, live = 0, freed = 0;
     auto refuse = [&] { ++calls; return (void *)nullptr; };
     auto grant = [&] { ++calls; return (void *)&memory; };
     oc::SplitWorkspace w, x;
     // no memory at the first call: never asked for again, also once there is some
-    CHECK(w.get(refuse) == nullptr && w.get(refuse) == nullptr && w.get(grant) == nullptr && calls == 1);
+    CHECK(w.get(live, refuse) == nullptr && w.get(live, refuse) == nullptr && w.get(live, grant) == nullptr && calls == 1);
     // memory at the first call: the same workspace ever after
     calls = 0;
-    CHECK(x.get(grant) == &memory && x.get(refuse) == &memory && calls == 1);
+    CHECK(x.get(live, grant) == &memory && x.get(live, refuse) == &memory && calls == 1);
+    // no more than MAX_SPLIT_WORKSPACES at a time; one given back makes room
+    oc::SplitWorkspace many[oc::MAX_SPLIT_WORKSPACES], y, z;
+    for (int i = 0; i + 1 < oc::MAX_SPLIT_WORKSPACES; ++i) CHECK(many[i].get(live, grant) == &memory);
+    CHECK(live == oc::MAX_SPLIT_WORKSPACES && y.get(live, grant) == nullptr);
+    auto release = [&](void *p) { freed += p == &memory; };
+    x.give_back(live, release);
+    w.give_back(live, release);
+    CHECK(freed == 1 && live == oc::MAX_SPLIT_WORKSPACES - 1);
+    CHECK(z.get(live, grant) == &memory && y.get(live, grant) == nullptr && live == oc::MAX_SPLIT_WORKSPACES);
     return 0;
 }
 """
 
 
-def test_workspace_is_asked_for_once(tmp_path):
+def test_workspaces_are_asked_for_once_and_bounded(tmp_path):
     src, exe = tmp_path / "t.cpp", tmp_path / "t"
     src.write_text(PROGRAM)
     subprocess.run([os.environ.get("CXX", "g++"), "-std=c++17", "-Wall", "-Werror", "-I",
