@@ -128,7 +128,11 @@ int launch_rest_of_layer(const LayerArgs &a, hipStream_t s) {
     // one product of the chain on m rows; with `act`, the gating as well
     auto product = [&](const uint16_t *x, const uint16_t *w, uint16_t *y, uint16_t *act, int64_t m, int64_t K,
                        int64_t N) -> int {
-        if (gemm_rows_applies(m, K, N, ws != nullptr)) {
+        // the fused gating writes act while x is still being read: where a
+        // caller lets act take x's memory (o is done with after this product),
+        // the gating follows the product
+        const bool apart = !act || act + m * (N / 2) <= x || x + m * K <= act;
+        if (apart && gemm_rows_applies(m, K, N, ws != nullptr)) {
             OC_HIP(launch_gemm_rows(x, w, y, act, ws, m, K, N, s));
             return OC_OK;
         }
