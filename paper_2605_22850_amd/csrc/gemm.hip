@@ -329,23 +329,32 @@ static hipError_t launch_glu(const GemmParams &p, const RowsPlan &r, hipStream_t
 }
 
 // Where these kernels take a product from the GEMM library, which does not
-// split K here (times in us on [H 4096, F 14336] products, ours with the
-// reduction / the library's):
-//  - few column tiles, so that K can be split and the library leaves CUs
-//    idle: down (K 14336, N 4096) 29/101 at 64 rows, 35/124 at 128, 56/106
-//    at 256, 93/140 at 512; N 4096, K 4096: 14/28, 17/40, 30/28, 38/45; past
-//    512 rows the two meet (140/153 and 50/49 at 768);
-//  - many column tiles (gate|up, N 28672, with the gating kernel behind the
-//    library's product): 47/59 at 1 row, 47/50 at 32, 52/52 at 64, then 62/57
-//    at 96 and 92/72 at 160: X moves through each CU once per column tile,
-//    and past 64 rows that costs more than the fused gating saves.
+// split K here.  The figures are us per product gained over the library's
+// (gate|up: over its product and the gating kernel), inside a whole layer whose
+// weights come from HBM, for layers of H/F 2048/5632, 2048/8192, 3584/18944,
+// 4096/14336, 5120/13824 and 8192/28672:
+//  - up to 64 rows, column tiles that fit the CUs in one go: O 4 to 28, down 12
+//    to 108, QKV 4 to 29; gate|up -5 to 17 (-5 at 32 and 64 rows of N 27648,
+//    the library's own tile sizes).  More column tiles than CUs leave a second
+//    round nearly empty: gate|up of N 37888 loses 21 to 24 (of 156 to 215 for
+//    the layer), of N 57344 32 to 44 (of 374 to 486);
+//  - to 512 rows where the tiles fill at most half the CUs, so that K is split
+//    and the library leaves CUs idle: down 8 to 131, but for N 3584, K 18944 at
+//    257 to 384 rows (-7 to -18); O -6 to 40, QKV -5 to 38.  257 to 384 rows are
+//    three tiles of 128 and 385 to 512 two of 256, so a product can be the
+//    library's in the first range and ours in the second: QKV of N 6144, K
+//    4096 would gain -3 to 0 in the first and gains -2 to 14 in the second,
+//    down of N 8192 -12 to -67 and 51 to 67, O of N 8192 0 to 5 and -6 to -3;
+//  - gate|up past 64 rows: X moves through each CU once per column tile, which
+//    costs more than the fused gating saves (N 28672: -17 at 192 rows, -58 at
+//    512); past 512 rows all products: O -35 to 4, down -190 to 46.
 // Without a workspace a product whose K would be split is the library's.
 bool gemm_rows_applies(int64_t M, int64_t K, int64_t N, bool has_workspace) {
     if (M < 1 || K < BK || K % BK || N % GEMM_BN || N < GEMM_BN) return false;
     // 32-bit offsets within a step's rows of W and a row tile of X
     if ((int64_t)BK * N * 2 >= INT32_MAX || 256 * K * 2 >= INT32_MAX) return false;
     const RowsPlan r = plan_rows(M, K, N);
-    if (M > 64 && (M > 512 || r.m_tiles * r.n_tiles * 2 > GEMM_WGS)) return false;
+    if (M > 512 || r.m_tiles * r.n_tiles * (M > 64 ? 2 : 1) > GEMM_WGS) return false;
     return has_workspace || r.n_split == 1;
 }
 

@@ -29,3 +29,14 @@ def test_no_product_is_split_without_a_workspace():
                 split += with_ws > 1
                 unsplit += without == 1
     assert split > 50 and unsplit > 20
+
+
+def test_few_row_products_fit_the_cus_at_once():
+    """Column tiles of 128 in one round over 256 CUs up to 64 rows, over half of
+    them to 512 rows (tiles of 128 rows at 257-384, else of 256)."""
+    for M, K, N, ours in ((1, 8192, 57344, False), (64, 3584, 37888, False), (64, 4096, 32768, True),
+                          (64, 4096, 32896, False), (64, 4096, 28672, True), (65, 4096, 28672, False),
+                          (128, 4096, 16384, True), (129, 4096, 16512, False), (256, 4096, 6144, True),
+                          (384, 4096, 6144, False), (385, 4096, 6144, True), (512, 14336, 4096, True),
+                          (513, 14336, 4096, False), (32, 4096, 100, False), (32, 100, 4096, False)):
+        assert (gemm_rows(M, K, N, 1) > 0) == ours, (M, K, N)
