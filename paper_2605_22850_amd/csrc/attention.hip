@@ -82,16 +82,33 @@ __device__ inline float half_swap_sum(float x) {
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
+// Whether all row tiles of a (KV head, split) group get consecutive slots on
+// one XCD (workgroup w runs on XCD w % 8), so that their K/V re-reads hit that
+// XCD's L2, or the tiles are dealt out to the XCDs one by one.
+//  - A multiple of 8 groups loads the XCDs evenly: by XCD.
+//  - 256-row tiles, any other count: dealt.  They re-read little, and XCDs that
+//    hold a group less idle (by XCD 0.95 to 1.82 times as long, 1.11 on
+//    average, over 87 shapes of 4 to 122 groups).
+//  - Tiles of 32 and 64 rows: by XCD where there is a group for every XCD and
+//    the busiest XCD's workgroups all run at once on its 32 CUs (0.60 to 1.05
+//    times as long as dealt, 0.94 on average, over 123 shapes of 9 to 108
+//    groups) or the XCDs are within 1/15 of even (0.48 to 1.12, 0.91 on average,
+//    over 36 shapes of 15 to 100 groups).  Otherwise the uneven XCDs cost more
+//    than their L2 gives (0.95 to 1.87, 1.28 on average, over 232 shapes), and
+//    with fewer groups than XCDs some would idle (1.0 to 6.3).
+__host__ __device__ inline bool tiles_by_xcd(int m_tiles, int n_groups, bool small_tiles) {
+    if ((n_groups & 7) == 0) return true;
+    const int per_xcd = (n_groups + 7) / 8;           // groups of the busiest XCD
+    return small_tiles && n_groups > 8 &&
+           ((int64_t)per_xcd * m_tiles <= 32 || 2 * (int64_t)n_groups >= 15 * (int64_t)per_xcd);
+}
+
 // Workgroup wg of a launch -> its (KV head, split) group and row tile; false
-// past the last.  Workgroup w runs on XCD w % 8.  With a multiple of 8 groups
-// all row tiles of a group get consecutive slots on one XCD, so their K/V
-// re-reads hit that XCD's L2.  With other counts that would leave XCDs idle
-// (4 groups: half of them), so the tiles are dealt out one by one.  Either
-// way the last row tile comes first: under the causal mask later rows see
-// more suffix keys, and dispatching the longest tiles first keeps them out of
-// the tail.
-__device__ inline bool tile_of(int wg, int m_tiles, int n_groups, int &gamma, int &mt) {
-    if (n_groups & 7) {
+// past the last.  Either way the last row tile comes first: under the causal
+// mask later rows see more suffix keys, and dispatching the longest tiles
+// first keeps them out of the tail.
+__host__ __device__ inline bool tile_of(int wg, int m_tiles, int n_groups, bool small_tiles, int &gamma, int &mt) {
+    if (!tiles_by_xcd(m_tiles, n_groups, small_tiles)) {
         gamma = wg % n_groups;
         mt = m_tiles - 1 - wg / n_groups;
         return mt >= 0;
@@ -261,7 +278,7 @@ __global__ __launch_bounds__(THREADS) void attn_fwd_kernel(KBatch batch) {
     const int col = lane & 31, half = lane >> 5;
 
     int gamma, mt;
-    if (!tile_of(wg, m_tiles, n_groups, gamma, mt)) return;
+    if (!tile_of(wg, m_tiles, n_groups, false, gamma, mt)) return;
     const int g = gamma / n_split, split = gamma - g * n_split;
 
     const int row = mt * TILE_ROWS + wave * WAVE_ROWS + col;
@@ -592,7 +609,7 @@ __global__ __launch_bounds__(NW * 64) void attn_ways_kernel(KParams p) {
     const int col = lane & 31, half = lane >> 5;
 
     int gamma, mt;
-    if (!tile_of((int)blockIdx.x, p.m_tiles, p.n_groups, gamma, mt)) return;
+    if (!tile_of((int)blockIdx.x, p.m_tiles, p.n_groups, true, gamma, mt)) return;
     const int g = gamma / p.n_split, split = gamma - g * p.n_split;
     const int rows = (int)p.rows, Tp = (int)p.Tp, Ts = (int)p.Ts, n_pre_pages = (int)p.n_pre_pages;
     const int grp = p.grp, nq = p.nq, nkv = p.nkv;
@@ -1096,7 +1113,16 @@ int plan_attention_batch(const oc_layout &lay, const int64_t *Tp, const int64_t 
     return OC_OK;
 }
 
-int64_t attention_grid(const AttnPlan &p) { return ((int64_t)p.nkv * p.n_split * p.m_tiles + 7) / 8 * 8; }
+int64_t attention_grid(const AttnPlan &p) {
+    const int64_t groups = (int64_t)p.nkv * p.n_split;
+    if (groups <= INT32_MAX && tiles_by_xcd(p.m_tiles, (int)groups, p.tile_rows != TILE_ROWS))
+        return (groups + 7) / 8 * 8 * p.m_tiles;
+    return (groups * p.m_tiles + 7) / 8 * 8;
+}
+
+bool attention_tile(int wg, const AttnPlan &p, int *group, int *row_tile) {
+    return tile_of(wg, p.m_tiles, p.nkv * p.n_split, p.tile_rows != TILE_ROWS, *group, *row_tile);
+}
 
 // a dispatch holds at most 2^32 - 1 work-items along x
 int64_t attention_max_grid() { return OC_MAX_GRID_ITEMS / THREADS; }

@@ -173,6 +173,8 @@ int check_attention_shape(const oc_layout &lay, int64_t Tp, int64_t Ts, AttnPlan
 int check_attention_args(const oc_layout &lay, int64_t Tp, int64_t Ts, AttnPlan *plan = nullptr);
 // workgroups of the attention launch of one plan
 int64_t attention_grid(const AttnPlan &p);
+// (KV head, split) group and row tile of one of them; false if it has none
+bool attention_tile(int wg, const AttnPlan &p, int *group, int *row_tile);
 // at most this many workgroups in one attention launch (all its requests)
 int64_t attention_max_grid();
 // LDS one attention workgroup holds at this head_dim (0: not supported)
