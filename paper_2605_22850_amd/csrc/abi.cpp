@@ -219,7 +219,7 @@ static int kv_layer_ingest_body(const oc_staging *staging, const oc_block_table 
         return fail(OC_EALIGN, "staging data and pool base must be 16-byte aligned");
     IngestArgs a = ingest_args(kv_pool, block_table, layer, staging->data);
     const int64_t n_pages = (block_table->num_tokens + l.page_size - 1) / l.page_size;
-    OC_HIP(launch_ingest(a, n_pages, static_cast<hipStream_t>(stream), false));
+    OC_HIP(launch_ingest(a, n_pages, static_cast<hipStream_t>(stream), 0));
     return OC_OK;
 }
 

@@ -711,7 +711,14 @@ __global__ __launch_bounds__(NW * 64) void attn_ways_kernel(KParams p) {
     int voff[NET];
 #pragma unroll
     for (int et = 0; et < NET; ++et) voff[et] = vt_offset<D>(lane, et);
-    const int krow = key_perm(col);
+    // LDS offsets of the S operands' first pieces; the piece of ds differs by XOR
+    // with ds * 16.  With Q in LDS they are made opaque in every round, so that
+    // the other pieces' offsets are computed and not kept: 243 -> 223 VGPRs, which
+    // leaves registers for one ingest wavefront per SIMD beside the attention's
+    // two (18400 + 63 tokens, 64 query heads, device-staged 907 -> 860 us over ten
+    // layers, 12208 + 83 with 32 query heads 631 -> 604; the attention alone is
+    // unchanged).
+    int k_at = k_lds<D>(key_perm(col), half), q_at = k_lds<D>(col, half);
 
     f32x16 o[QB][NET];
     float m[QB], l[QB];
@@ -737,12 +744,13 @@ __global__ __launch_bounds__(NW * 64) void attn_ways_kernel(KParams p) {
         f32x16 s[QB];
         {
             bf16x8 kf[NDS], qf[QB][NDS];
+            if constexpr (Sh::QLDS) asm volatile("" : "+v"(k_at), "+v"(q_at));
             auto load = [&](int ds) {
-                kf[ds] = *reinterpret_cast<const bf16x8 *>(&K[k_lds<D>(krow, ds * 2 + half)]);
+                kf[ds] = *reinterpret_cast<const bf16x8 *>(&K[k_at ^ (ds * 16)]);
 #pragma unroll
                 for (int qb = 0; qb < QB; ++qb)
                     if constexpr (Sh::QLDS)
-                        qf[qb][ds] = *reinterpret_cast<const bf16x8 *>(&q_lds[k_lds<D>(qb * 32 + col, ds * 2 + half)]);
+                        qf[qb][ds] = *reinterpret_cast<const bf16x8 *>(&q_lds[qb * 32 * D + (q_at ^ (ds * 16))]);
                     else
                         qf[qb][ds] = qop[qb][ds];
             };
@@ -1113,6 +1121,16 @@ int plan_attention_batch(const oc_layout &lay, const int64_t *Tp, const int64_t 
     return OC_OK;
 }
 
+int attention_registers(const AttnPlan &p) {
+    const void *f = reinterpret_cast<const void *>(
+        p.tile_rows == 32   ? (p.d == 128 ? &attn_ways_kernel<128, 1> : &attn_ways_kernel<64, 1>)
+        : p.tile_rows == 64 ? (p.d == 128 ? &attn_ways_kernel<128, 2> : &attn_ways_kernel<64, 2>)
+                            : nullptr);
+    if (!f) f = reinterpret_cast<const void *>(p.d == 128 ? &attn_fwd_kernel<128> : &attn_fwd_kernel<64>);
+    hipFuncAttributes a{};
+    return hipFuncGetAttributes(&a, f) == hipSuccess ? a.numRegs : -1;
+}
+
 int64_t attention_grid(const AttnPlan &p) {
     const int64_t groups = (int64_t)p.nkv * p.n_split;
     if (groups <= INT32_MAX && tiles_by_xcd(p.m_tiles, (int)groups, p.tile_rows != TILE_ROWS))
@@ -1127,8 +1145,10 @@ bool attention_tile(int wg, const AttnPlan &p, int *group, int *row_tile) {
 // a dispatch holds at most 2^32 - 1 work-items along x
 int64_t attention_max_grid() { return OC_MAX_GRID_ITEMS / THREADS; }
 
-size_t attention_lds_bytes(int head_dim) {
-    return head_dim == 64 ? attn_lds_bytes<64>() : head_dim == 128 ? attn_lds_bytes<128>() : 0;
+size_t attention_lds_bytes(const AttnPlan &p) {
+    if (p.tile_rows == 32) return p.d == 128 ? WaysShape<128, 1>::LDS : WaysShape<64, 1>::LDS;
+    if (p.tile_rows == 64) return p.d == 128 ? WaysShape<128, 2>::LDS : WaysShape<64, 2>::LDS;
+    return p.d == 128 ? attn_lds_bytes<128>() : attn_lds_bytes<64>();
 }
 
 int check_attention_shape(const oc_layout &l, int64_t Tp, int64_t Ts, AttnPlan *plan) {

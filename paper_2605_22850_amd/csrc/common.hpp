@@ -77,9 +77,13 @@ struct IngestArgs {
     int64_t region;            // pool_v - pool_k, elements
     int32_t d8, lg_d8, lg_ps, lg_nkv, lg_g;
 };
-// beside_compute: launched to run next to the attention kernel (more bytes in
-// flight per thread) rather than alone on the GPU
-hipError_t launch_ingest(IngestArgs a, int64_t n_pages_used, hipStream_t s, bool beside_compute);
+// beside_lds: 0 alone on the GPU; next to an attention kernel (more bytes in
+// flight per thread), the LDS that one of its workgroups holds
+hipError_t launch_ingest(IngestArgs a, int64_t n_pages_used, hipStream_t s, size_t beside_lds);
+// LDS that an ingest workgroup reserves next to workgroups holding that much
+size_t ingest_reservation(size_t beside_lds);
+// VGPRs of the ingest kernel that runs there, as the runtime reports them
+int ingest_registers(bool pow2);
 // every layer of whole chunk objects (n_layers, layer steps and token0 set)
 hipError_t launch_chunks_ingest(IngestArgs a, hipStream_t s);
 // arguments for chunks first_chunk .. first_chunk+num_chunks-1 of a request,
@@ -177,10 +181,12 @@ int64_t attention_grid(const AttnPlan &p);
 bool attention_tile(int wg, const AttnPlan &p, int *group, int *row_tile);
 // at most this many workgroups in one attention launch (all its requests)
 int64_t attention_max_grid();
-// LDS one attention workgroup holds at this head_dim (0: not supported)
-size_t attention_lds_bytes(int head_dim);
-// LDS of one compute unit on gfx950
-constexpr size_t CU_LDS_BYTES = 160 * 1024;
+// LDS one attention workgroup of the plan holds
+size_t attention_lds_bytes(const AttnPlan &p);
+// VGPRs of its kernel, as the runtime reports them (-1: no GPU)
+int attention_registers(const AttnPlan &p);
+// LDS of one compute unit on gfx950, and the unit it is handed out in
+constexpr size_t CU_LDS_BYTES = 160 * 1024, LDS_GRANULE = 1280;
 // one launch for up to MAX_ATTN_BATCH requests of one layer: keys are split
 // so that every workgroup gets about the same number of key blocks
 constexpr int MAX_ATTN_BATCH = 16;

@@ -10,8 +10,8 @@
 //    run): one piece per thread in payload order, so every wavefront reads
 //    1 KiB of the payload contiguously and writes four 256-byte rows, and
 //    many short wavefronts keep the most bytes in flight;
-//  - beside the attention kernel of an earlier layer, where two ingest
-//    wavefronts per SIMD run at the lowest issue priority: a thread takes
+//  - beside the attention kernel of an earlier layer, where one ingest
+//    wavefront per SIMD runs at the lowest issue priority: a thread takes
 //    8 slots x one 16-byte column of one (page, head) block and moves its K
 //    rows, then its V rows (8 loads in flight, one page lookup per 256 bytes
 //    moved, a shift decode of the thread's block and column).
@@ -258,20 +258,29 @@ static bool prepare(IngestArgs &a) {
     return p2;
 }
 
-hipError_t launch_ingest(IngestArgs a, int64_t n_pages_used, hipStream_t s, bool beside_compute) {
+// An ingest workgroup next to the attention reserves LDS (the kernel itself uses
+// none) so that one of them, one wavefront per SIMD, shares a CU with each
+// attention workgroup: more than half of what that leaves free, in the units
+// that LDS is handed out in, and never more than that, which would keep every
+// ingest waiting for CUs the attention does not hold.
+size_t ingest_reservation(size_t beside_lds) {
+    const size_t held = (beside_lds + LDS_GRANULE - 1) / LDS_GRANULE, all = CU_LDS_BYTES / LDS_GRANULE;
+    return beside_lds > 0 && held < all ? ((all - held) / 2 + 1) * LDS_GRANULE : 0;
+}
+
+int ingest_registers(bool pow2) {
+    hipFuncAttributes a{};
+    const void *f = reinterpret_cast<const void *>(pow2 ? &kv_ingest_rows_kernel<true> : &kv_ingest_rows_kernel<false>);
+    return hipFuncGetAttributes(&a, f) == hipSuccess ? a.numRegs : -1;
+}
+
+hipError_t launch_ingest(IngestArgs a, int64_t n_pages_used, hipStream_t s, size_t beside_lds) {
     if (n_pages_used == 0) return hipSuccess;
     const bool p2 = prepare(a);
-    if (beside_compute && a.token0 == 0) {
+    if (beside_lds > 0 && a.token0 == 0) {
         const int64_t n = n_pages_used * a.n_kv * (a.Ps / 8) * a.d8;
         const dim3 grid((unsigned)((n + kThreads - 1) / kThreads));
-        // Each workgroup reserves half the LDS an attention workgroup leaves
-        // free (the kernel itself uses none), so that at most two ingest
-        // workgroups, two wavefronts per SIMD, share a CU with the attention;
-        // registers alone would admit three.  With the attention's wavefronts
-        // issuing ahead of the ingest's, that is the count that moves the
-        // most bytes without lengthening the attention beside it.
-        const size_t attn = attention_lds_bytes(a.d);
-        const size_t lds = attn > 0 && attn < CU_LDS_BYTES ? (CU_LDS_BYTES - attn) / 2 : 0;
+        const size_t lds = ingest_reservation(beside_lds);
         if (p2 && a.Ps >= 8 && a.G >= 8)
             hipLaunchKernelGGL(kv_ingest_rows_kernel<true>, grid, dim3(kThreads), lds, s, a, n);
         else

@@ -60,4 +60,24 @@ int64_t oc_internal_attention_tiles(int32_t tile_rows, int32_t m_tiles, int32_t 
     return n;
 }
 
+// LDS that an attention workgroup holds, and what an ingest workgroup next to it
+// reserves.
+void oc_internal_lds(int32_t tile_rows, int32_t head_dim, int64_t *attention, int64_t *ingest) {
+    AttnPlan p{};
+    p.tile_rows = tile_rows;
+    p.d = head_dim;
+    *attention = (int64_t)attention_lds_bytes(p);
+    *ingest = (int64_t)ingest_reservation(attention_lds_bytes(p));
+}
+
+// VGPRs of an attention kernel and of the ingest kernel that runs next to it (a
+// GPU must be present).
+void oc_internal_registers(int32_t tile_rows, int32_t head_dim, int pow2_ingest, int32_t *attention, int32_t *ingest) {
+    AttnPlan p{};
+    p.tile_rows = tile_rows;
+    p.d = head_dim;
+    *attention = attention_registers(p);
+    *ingest = ingest_registers(pow2_ingest != 0);
+}
+
 }  // extern "C"

@@ -726,14 +726,14 @@ static int run_pipeline(Context *c, const oc_request *reqs, int32_t n_reqs, oc_r
     // on the compute stream, each layer's attention is one launch over all
     // of them (decided below, once the deliveries are known); its plans split
     // keys for all their row tiles together.
-    std::vector<AttnPlan> bplan(n_reqs);
+    std::vector<AttnPlan> plan(n_reqs), bplan(n_reqs);
     std::vector<size_t> bws_off(n_reqs, 0);
-    size_t ws_need = 0, bws_need = 0;
+    size_t ws_need = 0, bws_need = 0, attn_lds = 0;
     int64_t max_ts = 0;
     for (int32_t i = 0; i < n_reqs; ++i) {
-        AttnPlan p;
-        plan_attention(l, reqs[i].prefix_tokens, reqs[i].suffix_tokens, &p);
-        ws_need = std::max(ws_need, p.total);
+        plan_attention(l, reqs[i].prefix_tokens, reqs[i].suffix_tokens, &plan[i]);
+        ws_need = std::max(ws_need, plan[i].total);
+        attn_lds = std::max(attn_lds, attention_lds_bytes(plan[i]));
         max_ts = std::max(max_ts, reqs[i].suffix_tokens);
     }
     if (n_reqs >= 2 && n_reqs <= MAX_ATTN_BATCH) {
@@ -871,11 +871,8 @@ static int run_pipeline(Context *c, const oc_request *reqs, int32_t n_reqs, oc_r
     };
     // one layer's compute for request `ri` on `st`
     auto enqueue_attention = [&](int32_t ri, int32_t layer, hipStream_t st) -> hipError_t {
-        const oc_request &r = reqs[ri];
-        AttnPlan p;
-        plan_attention(l, r.prefix_tokens, r.suffix_tokens, &p);
         const AttnArgs a = attn_args(ri, layer, static_cast<unsigned char *>(c->ws) + (emu ? ri : 0) * ws_stride);
-        hipError_t e = launch_attention(p, a, st);
+        hipError_t e = launch_attention(plan[ri], a, st);
         if (e == hipSuccess && c->opts.append_suffix) e = launch_append(layer_append(ri, layer, a), st);
         return e == hipSuccess ? rest_of_layer(ri, layer, a, st) : e;
     };
@@ -915,6 +912,7 @@ static int run_pipeline(Context *c, const oc_request *reqs, int32_t n_reqs, oc_r
         for (int32_t i = 0; i < n_reqs; ++i) batch_grid += attention_grid(bplan[i]);
     const bool batched = !c->opts.attention_per_request && !emu && !by_rate && n_cw == 0 && n_reqs >= 2 &&
                          n_reqs <= MAX_ATTN_BATCH && batch_grid <= attention_max_grid();
+    if (batched) attn_lds = attention_lds_bytes(bplan[0]);
     std::vector<double> req_rate(n_reqs, 0.0), req_admit(n_reqs, 0.0);
     if (by_rate) {
         // rates and admissions by scheduling epoch; with every arrival at
@@ -1206,8 +1204,8 @@ static int run_pipeline(Context *c, const oc_request *reqs, int32_t n_reqs, oc_r
                 a.Ps = l.page_size;
                 // beside an attention: past the first item; batched, past the
                 // first layer, whose attention waits for all its ingests
-                e = launch_ingest(a, (bt.num_tokens + l.page_size - 1) / l.page_size, c->copy,
-                                  batched ? it.layer > 0 : step > 0);
+                const bool beside = batched ? it.layer > 0 : step > 0;
+                e = launch_ingest(a, (bt.num_tokens + l.page_size - 1) / l.page_size, c->copy, beside ? attn_lds : 0);
             }
             if (e == hipSuccess) e = hipEventRecord(ingested[k], c->copy);
             // batched: the copy stream runs in order, so the layer's last

@@ -79,3 +79,14 @@ def test_groups_that_stay_on_one_xcd():
                                    (64, 17, 14, False), (32, 8, 28, True), (32, 9, 28, False), (64, 5, 90, True),
                                    (32, 4, 6, False), (32, 16, 9, True), (32, 17, 9, False), (32, 200, 16, True)):
         assert by_xcd(rows, mt, groups) == want, (rows, mt, groups)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("tile_rows", [32, 64, 256])
+def test_one_ingest_workgroup_fits_beside_the_attention(tile_rows, d):
+    """LDS goes out in units of 1280 bytes, 128 to a CU; one ingest workgroup
+    shares a CU with an attention workgroup of any tile, two do not."""
+    attn, ingest = c_int64(), c_int64()
+    oc.lib().oc_internal_lds(tile_rows, d, ctypes.byref(attn), ctypes.byref(ingest))
+    held, reserved = -(-attn.value // 1280), -(-ingest.value // 1280)
+    assert held + reserved <= 128 < held + 2 * reserved

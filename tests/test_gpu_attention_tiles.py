@@ -54,3 +54,18 @@ def test_small_tiles_match_oracle(nq, nkv, d, Tp, Ts):
     got = from_dev(out)
     assert_attention_close(got if rows is None else got[rows], c.expected_attention(rows=rows),
                            f"nq {nq} nkv {nkv} d {d} Tp {Tp} Ts {Ts}")
+
+
+@pytest.mark.parametrize("pow2", [0, 1])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("tile", [32, 64, 256])
+def test_registers_leave_room_for_an_ingest_wavefront(tile, d, pow2):
+    """512 VGPRs per SIMD lane, handed out in eights: two attention wavefronts
+    and one of the ingest that runs beside them."""
+    import ctypes
+    import paper_2605_22850_amd as oc
+    print(f"[attention tiles] registers, tile {tile} d {d}", flush=True)
+    attn, ingest = ctypes.c_int32(), ctypes.c_int32()
+    oc.lib().oc_internal_registers(tile, d, pow2, ctypes.byref(attn), ctypes.byref(ingest))
+    assert attn.value > 0 and ingest.value > 0
+    assert 2 * (-(-attn.value // 8) * 8) + -(-ingest.value // 8) * 8 <= 512
