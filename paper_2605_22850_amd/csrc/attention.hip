@@ -607,6 +607,9 @@ __global__ __launch_bounds__(NW * 64) void attn_ways_kernel(KParams p) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = lane & 31, half = lane >> 5;
+    // ahead of ingest wavefronts on the same SIMD, as the kernel above (no
+    // difference in a run's time was measured: they meet at L2, not at issue)
+    __builtin_amdgcn_s_setprio(1);
 
     int gamma, mt;
     if (!tile_of((int)blockIdx.x, p.m_tiles, p.n_groups, true, gamma, mt)) return;
