@@ -7,6 +7,7 @@ import numpy as np
 import pytest
 
 import paper_2605_22850_amd as oc
+from tests.attention_cases import BATCHES, BY_PLAN, RAGGED
 
 
 def gemm_rows(M, K, N, has_workspace):
@@ -90,3 +91,58 @@ def test_one_ingest_workgroup_fits_beside_the_attention(tile_rows, d):
     oc.lib().oc_internal_lds(tile_rows, d, ctypes.byref(attn), ctypes.byref(ingest))
     held, reserved = -(-attn.value // 1280), -(-ingest.value // 1280)
     assert held + reserved <= 128 < held + 2 * reserved
+
+
+def attention_plan(nq, nkv, d, Tp, Ts):
+    """(tile rows, row tiles, key blocks, splits, blocks per split)"""
+    lay = oc.Layout(1, nq, nkv, d, 16, 16, max(1, -(-Tp // 16))).c()
+    out = (c_int64 * 5)()
+    assert oc.lib().oc_internal_attention_plan(ctypes.byref(lay), c_int64(Tp), c_int64(Ts), out) == 0
+    return tuple(out)
+
+
+def place_of_partial_page(Tp, n_blocks, per_range, pages_per_block):
+    """Where in its range of key blocks the prefix's partial page lies."""
+    block = Tp // 16 // pages_per_block
+    at, last = block % per_range, min(per_range, n_blocks - block // per_range * per_range) - 1
+    return "only" if last == 0 else "first" if at == 0 else "last" if at == last else "middle"
+
+
+@pytest.mark.parametrize("tile,d,split", list(BY_PLAN))
+def test_attention_cases_take_the_kernel_they_name(tile, d, split):
+    odd = set()
+    for case in BY_PLAN[tile, d, split]:
+        rows, _, _, n_split, _ = attention_plan(*case)
+        assert (rows, case[2], n_split > 1) == (tile, d, split), (case, rows, n_split)
+        odd.add(case[1] * n_split % 8 != 0)
+    assert True in odd or (tile, d, split) == (256, 64, False)      # groups that do not load the XCDs evenly
+
+
+@pytest.mark.parametrize("tile,d", list(RAGGED))
+def test_ragged_prefixes_take_the_kernel_they_name(tile, d):
+    places = set()
+    for case in RAGGED[tile, d]:
+        rows, _, n_blocks, _, per_range = attention_plan(*case)
+        assert (rows, case[2]) == (tile, d), (case, rows)
+        assert tile < 256 or per_range >= 5
+        places.add(place_of_partial_page(case[3], n_blocks, per_range, 4 if tile == 256 else 2))
+    assert {case[3] % 16 for case in RAGGED[tile, d]} == {1, 5, 8, 15}
+    assert tile < 256 or places == {"first", "middle", "last"}
+
+
+def test_batches_cover_ranges_of_one_to_many_blocks():
+    places, slots = set(), set()
+    for nq, nkv, Tp, Ts, per_range in BATCHES:
+        for d in (64, 128):
+            n = len(Tp)
+            lay = oc.Layout(1, nq, nkv, d, 16, 16, 1000).c()
+            out = (c_int64 * (5 * n))()
+            assert oc.lib().oc_internal_attention_batch_plan(ctypes.byref(lay), n, (c_int64 * n)(*Tp), (c_int64 * n)(*Ts),
+                                                             out) == 0
+            plans = [out[5 * i:5 * i + 5] for i in range(n)]
+            assert {p[0] for p in plans} == {256} and {p[4] for p in plans} == per_range, (nq, nkv, plans)
+            for t, p in zip(Tp, plans):
+                if t % 16:
+                    places.add(place_of_partial_page(t, p[2], p[4], 4))
+                    slots.add(t % 16)
+    assert places == {"only", "first", "middle", "last"} and slots >= {1, 5, 8, 15}

@@ -80,8 +80,9 @@ def test_row_tiles(T):
 
 
 # one K step; ffn sizes that leave the last split short; products the library
-# keeps (N or K not whole tiles); the 8B layer on both sides of the unsplit limit
-SHAPES = [(4, 4, 64, 64, 5), (8, 8, 64, 1728, 40), (8, 2, 128, 832, 100), (4, 1, 64, 72, 9), (6, 2, 24, 40, 33),
+# keeps (N or K not whole tiles); the 8B layer on both sides of the unsplit
+# limit; gate|up of as many column tiles as CUs, and of more (the library's)
+SHAPES = [(4, 1, 64, 16384, 9), (4, 1, 64, 16512, 9), (4, 4, 64, 64, 5), (8, 8, 64, 1728, 40), (8, 2, 128, 832, 100), (4, 1, 64, 72, 9), (6, 2, 24, 40, 33),
           (32, 8, 128, 14336, 64), (32, 8, 128, 14336, 65)]
 
 
