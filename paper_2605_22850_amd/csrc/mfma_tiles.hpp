@@ -36,8 +36,8 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 // Workgroup barrier that waits only for this wavefront's LDS operations.
-// (__syncthreads() would also wait for every outstanding global load, which
-// would stall the register prefetch of the block after next.)
+// (__syncthreads() would also wait for every outstanding global -> LDS copy, and
+// so for the tiles that are being fetched ahead.)
 __device__ inline void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 // LDS element offset of 16-byte column c of K tile row r (D/8 columns per row)
@@ -65,10 +65,15 @@ typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
 // assembly on purpose: the compiler treats every outstanding global->LDS copy
 // as a possible writer of any LDS address, and would make each operand read
 // of the current tile wait (vmcnt(0)) for the copies of the blocks still in
-// flight, which serialises the prefetch.  The kernel orders these copies
-// itself: wait_vmcnt before the per-block barrier, which is the only point
-// where a tile becomes readable, and a buffer is refilled only after every
-// wavefront has passed the barrier that follows its last read.
+// flight, which serialises the prefetch.  The kernels order these copies
+// themselves:
+//  - a tile that the whole workgroup reads (256-row attention, GEMM): every
+//    wavefront waits for its own copies (wait_vmcnt), then a barrier makes the
+//    tile readable; it is refilled only after a barrier that follows its last
+//    read;
+//  - a ring of one wavefront's own (attention tiles of 32 and 64 rows): that
+//    wavefront's wait_vmcnt before it reads, and s_waitcnt lgkmcnt(0) after its
+//    last read, before it refills.  No barrier stands in for either.
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"   // m0 is written here and read by nothing else in these kernels
 __device__ inline void dma16(const void *base, uint32_t lane_off, uint16_t *lds_chunk) {
