@@ -52,6 +52,20 @@ def test_prefixes_that_end_inside_a_page(nq, nkv, d, Tp, Ts):
     _check(nq, nkv, d, Tp, Ts)
 
 
+@pytest.mark.parametrize("nq,nkv,d,Tp,Ts", [cases[-1] for cases in BY_PLAN.values()])
+def test_a_call_repeats_itself_bit_for_bit(nq, nkv, d, Tp, Ts):
+    import torch
+    print(f"[attention tiles] twice: nq {nq} nkv {nkv} d {d} Tp {Tp} Ts {Ts}", flush=True)
+    G = 8 if Tp % 8 == 0 else Tp
+    c = LayerCase(nq, nkv, d, G, 16, Tp // G, Ts, -(-Tp // 16) + 5, 1, 0, seed=Ts).upload()
+    c.run_ingest()
+    first = c.run_attention()
+    for _ in range(4):
+        again = c.run_attention()
+        torch.cuda.synchronize()
+        assert torch.equal(first.view(torch.int16), again.view(torch.int16))
+
+
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("nq,nkv,Tp,Ts", [b[:4] for b in BATCHES])
 def test_batched_launch_with_prefixes_that_end_inside_a_page(nq, nkv, Tp, Ts, d):

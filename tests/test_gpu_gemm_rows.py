@@ -82,8 +82,8 @@ def test_row_tiles(T):
 # one K step; ffn sizes that leave the last split short; products the library
 # keeps (N or K not whole tiles); the 8B layer on both sides of the unsplit
 # limit; gate|up of as many column tiles as CUs, and of more (the library's)
-SHAPES = [(4, 1, 64, 16384, 9), (4, 1, 64, 16512, 9), (4, 4, 64, 64, 5), (8, 8, 64, 1728, 40), (8, 2, 128, 832, 100), (4, 1, 64, 72, 9), (6, 2, 24, 40, 33),
-          (32, 8, 128, 14336, 64), (32, 8, 128, 14336, 65)]
+SHAPES = [(4, 4, 64, 64, 5), (8, 8, 64, 1728, 40), (8, 2, 128, 832, 100), (4, 1, 64, 72, 9), (6, 2, 24, 40, 33),
+          (32, 8, 128, 14336, 64), (32, 8, 128, 14336, 65), (4, 1, 64, 16384, 9), (4, 1, 64, 16512, 9)]
 
 
 @pytest.mark.parametrize("nq,nkv,d,F,T", SHAPES)
@@ -92,6 +92,22 @@ def test_shapes(nq, nkv, d, F, T):
     c = Layer(nq, nkv, d, F, T, seed=F + T)
     c.run()
     c.check(f"F {F} T {T}")
+
+
+@pytest.mark.parametrize("T", [1, 40, 130, 400])
+def test_a_call_repeats_itself_bit_for_bit(T):
+    import torch
+    print(f"[gemm rows] twice, T {T}", flush=True)
+    c = Layer(32, 8, 128, 2048, T, seed=60)
+    c.run()
+    torch.cuda.synchronize()
+    want = [b.clone() for b in c.bufs]
+    for _ in range(4):
+        for b in c.bufs:
+            b[:T].fill_(3.0)
+        c.run()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(c.bufs, want))
 
 
 def test_streams_do_not_share_partials():
