@@ -247,12 +247,13 @@ typedef struct {
  * attention output, as oc_suffix_prefill_layer writes it).  tokens == 0 is
  * not an error.  Asynchronous on `stream`.  The library keeps a GEMM library
  * handle per stream and, for the partial sums of products whose K it splits, a
- * 32 MiB workspace (at most 64 of these in a process); the first eager call on
- * a stream makes both (it allocates; later calls on that stream do not, under
- * capture or not).  Calls under stream capture and on hipStreamPerThread use no
- * workspace, since their kernels may run beside other calls' on the same stream
- * handle: graphs captured on one stream may be replayed together, on any
- * streams.  Without a workspace, products that would be split go to the GEMM
+ * 32 MiB workspace; the first eager call on a stream makes both (it allocates;
+ * later eager calls on that stream do not).  Calls under stream capture put
+ * their partial sums into a workspace of that capture's own, made by the first
+ * that needs one and kept until the process ends, so graphs captured on one
+ * stream may be replayed together, on any streams, and beside eager calls.  A
+ * process makes at most 64 workspaces; without one, and on hipStreamPerThread
+ * (one handle for many queues), products that would be split go to the GEMM
  * library, with the same rounding points but another order of fp32 sums.
  * A stream's calls must have finished before it is destroyed. */
 int oc_rest_of_layer(const void *attn_out, int64_t tokens, const oc_layout *layout,

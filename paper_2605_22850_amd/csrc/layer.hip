@@ -40,16 +40,13 @@ __global__ __launch_bounds__(256) void silu_mul_kernel(const uint16_t *gu, uint1
     *reinterpret_cast<u32x4 *>(act + t * 8 * F8 + c * 8) = __builtin_bit_cast(u32x4, __builtin_convertvector(r, bf16x8));
 }
 
-// Per (device, stream): a rocBLAS handle and the few-row GEMM's workspace for
-// split partials, both made by the first eager call on the stream, whichever of
-// them its row count needs.  They live until the process ends, or until
-// forget_blas_stream() for streams the library owns.
-//
-// The workspace serves one call at a time because calls on one stream run in
-// order.  That does not hold for a captured call (its graph may be replayed on
-// any stream, beside other graphs captured on this one and beside eager calls)
-// nor for hipStreamPerThread (one handle, a queue per host thread): these get
-// no workspace, and products that would need one go to the GEMM library.
+// Per (device, stream): a rocBLAS handle and the few-row GEMM's workspaces for
+// split partials.  The first eager call on the stream makes the handle and the
+// eager calls' workspace, whichever of them its row count needs; they live until
+// the process ends, or until forget_blas_stream() for streams the library owns.
+// hipStreamPerThread is one handle for a queue per host thread, whose calls may
+// overlap: it gets no workspace, and products that would need one go to the
+// GEMM library.
 struct StreamState {
     rocblas_handle handle = nullptr;
     SplitWorkspace ws;
@@ -58,15 +55,41 @@ static std::mutex g_blas_mu;
 static std::map<std::pair<int, hipStream_t>, StreamState> g_blas;
 static int g_workspaces = 0;
 
-static bool capturing(hipStream_t s) {
-    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
-    (void)hipGetLastError();      // the null stream while another captures: the launches report it
-    return false;
+static void *allocate_workspace() {
+    void *p = nullptr;
+    if (hipMalloc(&p, GEMM_WORKSPACE_BYTES) == hipSuccess) return p;
+    (void)hipGetLastError();
+    return nullptr;
 }
 
-// the stream's handle, and the workspace that this call may use (or NULL)
-static int stream_state(hipStream_t s, rocblas_handle *handle, void **ws) {
+// the same while a stream captures, which an allocation on this thread would
+// otherwise end
+static void *allocate_workspace_under_capture() {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    void *const p = allocate_workspace();
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    return p;
+}
+
+// the stream's handle, and where the call's split partials go
+struct CallState {
+    rocblas_handle handle = nullptr;
+    SplitWorkspace *ws = nullptr;           // NULL: nowhere
+    bool capturing = false;
+    unsigned long long capture = 0;
+
+    void *workspace() const {
+        if (!ws) return nullptr;
+        return capturing ? ws->get_captured(g_workspaces, capture, allocate_workspace_under_capture)
+                         : ws->get(g_workspaces, allocate_workspace);
+    }
+};
+
+static int stream_state(hipStream_t s, CallState *out) {
     int dev = 0;
     OC_HIP(hipGetDevice(&dev));
     StreamState *st = &g_blas[std::make_pair(dev, s)];
@@ -75,15 +98,18 @@ static int stream_state(hipStream_t s, rocblas_handle *handle, void **ws) {
         return fail(OC_EHIP, "rocblas_create_handle failed");
     }
     if (rocblas_set_stream(st->handle, s) != rocblas_status_success) return fail(OC_EHIP, "rocblas_set_stream failed");
-    *handle = st->handle;
-    *ws = nullptr;
-    if (s == hipStreamPerThread || capturing(s)) return OC_OK;
-    *ws = st->ws.get(g_workspaces, [] {
-        void *p = nullptr;
-        if (hipMalloc(&p, GEMM_WORKSPACE_BYTES) == hipSuccess) return p;
-        (void)hipGetLastError();
-        return (void *)nullptr;
-    });
+    out->handle = st->handle;
+    if (s == hipStreamPerThread) return OC_OK;
+    out->ws = &st->ws;
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamGetCaptureInfo(s, &status, &out->capture) != hipSuccess) {
+        (void)hipGetLastError();      // the null stream while another captures: the launches report it
+        out->ws = nullptr;
+    } else if (status != hipStreamCaptureStatusNone) {
+        out->capturing = true;
+    } else {
+        (void)out->workspace();
+    }
     return OC_OK;
 }
 
@@ -119,9 +145,8 @@ static int gemm(rocblas_handle h, const uint16_t *X, const uint16_t *W, uint16_t
 int launch_rest_of_layer(const LayerArgs &a, hipStream_t s) {
     if (a.T == 0) return OC_OK;
     std::lock_guard<std::mutex> g(g_blas_mu);
-    rocblas_handle handle = nullptr;
-    void *ws = nullptr;
-    int rc = stream_state(s, &handle, &ws);
+    CallState call;
+    int rc = stream_state(s, &call);
     if (rc) return rc;
     const int64_t widest = std::max(std::max(2 * a.F, a.H), a.NQKV);
     const int64_t rb = std::max<int64_t>(1, (INT64_C(1) << 29) / widest);
@@ -132,11 +157,14 @@ int launch_rest_of_layer(const LayerArgs &a, hipStream_t s) {
         // caller lets act take x's memory (o is done with after this product),
         // the gating follows the product
         const bool apart = !act || act + m * (N / 2) <= x || x + m * K <= act;
-        if (apart && gemm_rows_applies(m, K, N, ws != nullptr)) {
-            OC_HIP(launch_gemm_rows(x, w, y, act, ws, m, K, N, s));
-            return OC_OK;
+        if (apart && gemm_rows_applies(m, K, N, true)) {
+            void *const ws = gemm_rows_splits(m, K, N) > 1 ? call.workspace() : nullptr;
+            if (gemm_rows_applies(m, K, N, ws != nullptr)) {
+                OC_HIP(launch_gemm_rows(x, w, y, act, ws, m, K, N, s));
+                return OC_OK;
+            }
         }
-        const int r = gemm(handle, x, w, y, m, K, N);
+        const int r = gemm(call.handle, x, w, y, m, K, N);
         if (r) return r;
         if (act) {
             const int64_t n = m * (N / 16);

@@ -20,8 +20,8 @@ def gemm_rows(M, K, N, has_workspace):
 
 
 def test_no_product_is_split_without_a_workspace():
-    """Captured calls and the per-thread stream have no workspace of their own:
-    their products are unsplit or the library's."""
+    """Calls on the per-thread stream, and those past the number of workspaces,
+    have none: their products are unsplit or the library's."""
     split = unsplit = 0
     for M in (1, 31, 32, 33, 64, 65, 128, 129, 256, 257, 512, 513, 4096):
         for K in (64, 192, 256, 512, 1792, 4096, 14336, 28672):

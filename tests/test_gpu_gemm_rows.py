@@ -132,45 +132,18 @@ def test_under_capture():
     with torch.cuda.stream(s):
         c.run(s)            # the stream's workspace is made before the capture
     torch.cuda.synchronize()
+    want = [b.clone() for b in c.bufs]
     g = torch.cuda.CUDAGraph()
     with torch.cuda.graph(g, stream=s):
         c.run(s)
-    # a captured call has no split partials, so its sums may differ from the
-    # eager call's in order; every replay repeats the first bit for bit
-    want = None
     for k in range(4):
         for b in c.bufs:
             b[:c.T].fill_(float(k))
         torch.cuda.synchronize()
         g.replay()
         torch.cuda.synchronize()
-        if want is None:
-            want = [b.clone() for b in c.bufs]
         assert all(torch.equal(a, b) for a, b in zip(c.bufs, want)), f"replay {k}"
         c.check(f"replay {k}")
-
-
-def test_unsplit_products_under_capture_equal_eager():
-    # K of 4 steps at most (H 256, F 256): no product is split, so the captured
-    # call runs the same kernels as the eager one
-    import torch
-    print("[gemm rows] captured, no splits", flush=True)
-    c = Layer(4, 1, 64, 256, 40, seed=12)
-    s = torch.cuda.Stream()
-    with torch.cuda.stream(s):
-        c.run(s)
-    torch.cuda.synchronize()
-    want = [b.clone() for b in c.bufs]
-    g = torch.cuda.CUDAGraph()
-    with torch.cuda.graph(g, stream=s):
-        c.run(s)
-    for k in range(3):
-        for b in c.bufs:
-            b[:c.T].fill_(float(k))
-        torch.cuda.synchronize()
-        g.replay()
-        torch.cuda.synchronize()
-        assert all(torch.equal(a, b) for a, b in zip(c.bufs, want)), f"replay {k}"
 
 
 @pytest.mark.parametrize("T,offset", [(40, 0), (64, 256), (1, 0), (200, 64)])

@@ -30,6 +30,18 @@ int main() {
     w.give_back(live, release);
     CHECK(freed == 1 && live == oc::MAX_SPLIT_WORKSPACES - 1);
     CHECK(z.get(live, grant) == &memory && y.get(live, grant) == nullptr && live == oc::MAX_SPLIT_WORKSPACES);
+    // a capture's own: not the stream's, not the capture before's; asked for once
+    live = 0;
+    calls = 0;
+    int other = 0;
+    oc::SplitWorkspace c;
+    CHECK(c.get(live, grant) == &memory && calls == 1);
+    auto second = [&] { ++calls; return (void *)&other; };
+    CHECK(c.get_captured(live, 0, second) == &other && c.get_captured(live, 0, grant) == &other && calls == 2);
+    CHECK(c.get_captured(live, 7, refuse) == nullptr && c.get_captured(live, 7, grant) == nullptr && calls == 3);
+    CHECK(c.get_captured(live, 8, grant) == &memory && live == 3 && c.get(live, refuse) == &memory && calls == 4);
+    live = oc::MAX_SPLIT_WORKSPACES;
+    CHECK(c.get_captured(live, 9, grant) == nullptr && calls == 4);
     return 0;
 }
 """
