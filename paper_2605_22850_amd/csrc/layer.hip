@@ -55,23 +55,16 @@ static std::mutex g_blas_mu;
 static std::map<std::pair<int, hipStream_t>, StreamState> g_blas;
 static int g_workspaces = 0;
 
+// In relaxed mode: a plain allocation would end this stream's capture, and fail
+// beside another thread's.
 static void *allocate_workspace() {
     void *p = nullptr;
-    if (hipMalloc(&p, GEMM_WORKSPACE_BYTES) == hipSuccess) return p;
-    (void)hipGetLastError();
-    return nullptr;
-}
-
-// the same while a stream captures, which an allocation on this thread would
-// otherwise end
-static void *allocate_workspace_under_capture() {
     hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-    if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) {
-        (void)hipGetLastError();
-        return nullptr;
+    if (hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess) {
+        if (hipMalloc(&p, GEMM_WORKSPACE_BYTES) != hipSuccess) p = nullptr;
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
     }
-    void *const p = allocate_workspace();
-    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (!p) (void)hipGetLastError();
     return p;
 }
 
@@ -84,7 +77,7 @@ struct CallState {
 
     void *workspace() const {
         if (!ws) return nullptr;
-        return capturing ? ws->get_captured(g_workspaces, capture, allocate_workspace_under_capture)
+        return capturing ? ws->get_captured(g_workspaces, capture, allocate_workspace)
                          : ws->get(g_workspaces, allocate_workspace);
     }
 };
