@@ -82,14 +82,15 @@ __device__ inline float half_swap_sum(float x) {
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-// Zero n rows of an LDS tile, 16 bytes per store, by the `count` lanes of which
-// this is number `at`.  (One wavefront clearing two bytes per store and lane
-// took some 0.5 us of a 7 us call: 20 + 6 tokens, d = 128, 6.6 -> 6.1.)
+// Zero n rows of an LDS tile with one wavefront, 16 bytes per lane and store.
+// (Two bytes took some 0.5 us of a 7 us call: 20 + 6 tokens, d = 128, 6.6 -> 6.1.
+// The 256-row kernel clears with 256 lanes and two bytes: this way its loop ran
+// 0.1 to 0.3 % slower.)
 template <int D>
-__device__ __forceinline__ void clear_rows(uint16_t *rows, int n, int at, int count) {
+__device__ __forceinline__ void clear_rows(uint16_t *rows, int n, int lane) {
     uint32_t z = 0;
     asm volatile("" : "+v"(z));      // made here: the compiler would keep four registers of zeros through the loop
-    for (int i = at; i < n * (D / 8); i += count) *reinterpret_cast<u32x4 *>(rows + i * 8) = u32x4{z, z, z, z};
+    for (int i = lane; i < n * (D / 8); i += 64) *reinterpret_cast<u32x4 *>(rows + i * 8) = u32x4{z, z, z, z};
 }
 
 // Whether all row tiles of a (KV head, split) group get consecutive slots on
@@ -472,7 +473,7 @@ __global__ __launch_bounds__(THREADS) void attn_fwd_kernel(KBatch batch) {
         if (j < nb && (b + 1) * 4 > full_pre_pages && b * 4 <= full_pre_pages && full_pre_pages < n_pre_pages) {
             uint16_t *V = lds + (j % NBUF) * 2 * TILE + TILE;
             const int pg = full_pre_pages - b * 4, k0 = Tp % PAGE;
-            clear_rows<D>(V + (pg * PAGE + k0) * D, PAGE - k0, tid - THREADS / 2, THREADS / 2);
+            for (int idx = tid - THREADS / 2; idx < D * (PAGE - k0); idx += THREADS / 2) V[(pg * PAGE + k0) * D + idx] = 0;
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         }
     };
@@ -841,7 +842,7 @@ __global__ __launch_bounds__(NW * 64) void attn_ways_kernel(KParams p) {
             // zero the partial prefix page's slots past Tp, which may hold
             // anything: masked keys then contribute exactly nothing
             const int pg = full_pre_pages - u * 2, k0 = Tp % PAGE;
-            clear_rows<D>(V + (pg * PAGE + k0) * D, PAGE - k0, lane, 64);
+            clear_rows<D>(V + (pg * PAGE + k0) * D, PAGE - k0, lane);
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         }
         {
